@@ -10,6 +10,14 @@
 #define PXCL_HD
 #endif
 
+// Address space of the device pointers below as the kernels see them (global memory in
+// their device compilation, nothing elsewhere): a pointer that the kernels read from
+// memory would otherwise be a generic one, and every access through it a flat
+// instruction, whose completion each wait for LDS includes.
+#ifndef PXCL_G
+#define PXCL_G
+#endif
+
 namespace pxcl {
 
 typedef uint8_t u8;
@@ -92,20 +100,20 @@ constexpr u32 EF_HITS = 2;       // hits fused into the clustering: every kept d
 
 // One event as the kernels see it (144 bytes).
 struct EventDesc {
-    const u16* module;   // digis grouped by module (the input, or the workspace's grouped copy)
-    const u16* row;
-    const u16* col;
-    const u16* adc;
-    const u16* r_module; // with EF_UNSORTED: the digis as given (any order)
-    const u16* r_row;
-    const u16* r_col;
-    const u16* r_adc;
-    u8* ws;              // event workspace (device)
-    u32* hstat;          // status block (pinned host memory or device memory)
-    int32_t* o_digi;     // per-digi cluster ids [n], in input order
-    int32_t* o_id;       // kept clusters (ascending id); room for n entries each, used as
-    int32_t* o_charge;   // per-cluster temporaries of the big-module kernel's scratch mode
-    int32_t* o_size;
+    const u16 PXCL_G* module;   // digis grouped by module (the input, or the workspace's grouped copy)
+    const u16 PXCL_G* row;
+    const u16 PXCL_G* col;
+    const u16 PXCL_G* adc;
+    const u16 PXCL_G* r_module; // with EF_UNSORTED: the digis as given (any order)
+    const u16 PXCL_G* r_row;
+    const u16 PXCL_G* r_col;
+    const u16 PXCL_G* r_adc;
+    u8 PXCL_G* ws;              // event workspace (device)
+    u32 PXCL_G* hstat;          // status block (pinned host memory or device memory)
+    int32_t PXCL_G* o_digi;     // per-digi cluster ids [n], in input order
+    int32_t PXCL_G* o_id;       // kept clusters (ascending id); room for n entries each, used as
+    int32_t PXCL_G* o_charge;   // per-cluster temporaries of the big-module kernel's scratch mode
+    int32_t PXCL_G* o_size;
     u32 n;               // digis
     u32 cap;             // workspace capacity in digis
     u32 epoch;           // launch tag of the module-table words
@@ -127,8 +135,8 @@ constexpr u32 HDR_EV_OFFSET = 64;
 PXCL_HD inline size_t header_bytes(u32 max_events) { return HDR_EV_OFFSET + size_t(max_events) * sizeof(EventDesc); }
 
 struct LaunchArgs {
-    const u32* hdr;     // batch header (device) or nullptr: then `single` is the only event
-    u32* ctr;           // N_CTR launch counters (device)
+    const u32 PXCL_G* hdr;   // batch header (device) or nullptr: then `single` is the only event
+    u32 PXCL_G* ctr;         // N_CTR launch counters (device)
     u32 n_modules;
     u32 charge_cut;
     u32 dcap;           // largest module (digis) the small-module kernel takes

@@ -41,6 +41,14 @@
 // invalidate the L2.
 #include <hip/hip_runtime.h>
 
+#if defined(__AMDGCN__)
+#define PXCL_G __attribute__((address_space(1)))
+#define PXCL_C __attribute__((address_space(4)))   // constant: read-only while the kernel runs
+// As flat accesses (163 of them in the 256x1 small kernel) instead of global ones the
+// kernels took 1-4 % longer: one 320k-digi x 16 launch 421 us, now 414 us.
+#else
+#define PXCL_C
+#endif
 #include "pxcl_internal.h"
 
 namespace pxcl {
@@ -91,12 +99,15 @@ __device__ __forceinline__ void lds_barrier() { gsync<128>(); }
 
 __device__ __forceinline__ u32 num_events(const LaunchArgs& a) { return a.hdr ? a.hdr[0] : 1u; }
 __device__ __forceinline__ EventDesc get_event(const LaunchArgs& a, u32 e) {
-    return a.hdr ? reinterpret_cast<const EventDesc*>(reinterpret_cast<const u8*>(a.hdr) + HDR_EV_OFFSET)[e]
-                 : a.single;
+    // the header is not written while a kernel runs: with e the same for a whole wave its
+    // fields come by scalar loads
+    const EventDesc* d = (const EventDesc*)(const EventDesc PXCL_C*)(reinterpret_cast<uintptr_t>(a.hdr) + HDR_EV_OFFSET);
+    return a.hdr ? d[e] : a.single;
 }
+__device__ __forceinline__ u32* ticket(const LaunchArgs& a) { return (u32*)(a.ctr + S_TICK); }
 template <typename T>
 __device__ __forceinline__ T* ws_ptr(const EventDesc& E, size_t off) {
-    return reinterpret_cast<T*>(E.ws + off);
+    return (T*)(T PXCL_G*)(E.ws + off);         // generic again, but known to be global
 }
 // Digis in any order: the input position of grouped digi p is perm[p]; per-digi
 // outputs go there.  nullptr when the digis came grouped (position p itself).
@@ -417,13 +428,13 @@ __global__ __launch_bounds__(G_WG) void k_group_count(LaunchArgs a) {
     const u32 total = event_prefix<G_WG>(a, k, s_pref, s_wsum, CNT_ANY, G_CH, 0);
     // the small kernel's ticket starts at zero (segmentation, which also resets it,
     // is not launched when every event of the launch is in any order)
-    if (blockIdx.x == 0 && tid == 0) st_ag(&a.ctr[S_TICK], 0u);
+    if (blockIdx.x == 0 && tid == 0) st_ag(ticket(a), 0u);
     for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
         const u32 e = find_slot(s_pref, k, t), c = t - s_pref[e];
         const EventDesc E = get_event(a, e);
         const EvLayout L = ev_layout(E.cap, M);
         u32* gcnt = ws_ptr<u32>(E, L.gcnt);
-        u32* rank = reinterpret_cast<u32*>(E.o_digi);
+        u32* rank = (u32*)E.o_digi;
         if (tid == 0) s_err = 0;
         if (lds)
             for (u32 m = tid; m < M; m += G_WG) hist[m] = 0u;
@@ -540,7 +551,7 @@ __global__ __launch_bounds__(G_WG) void k_group_scatter(LaunchArgs a) {
         const EventDesc E = get_event(a, e);
         const EvLayout L = ev_layout(E.cap, M);
         const ModRange* mt = ws_ptr<const ModRange>(E, L.mtab);
-        const u32* rank = reinterpret_cast<const u32*>(E.o_digi);
+        const u32* rank = (const u32*)E.o_digi;
         const GroupArrays G = group_arrays(E, L);
         // every load first (module ids, then table entries, ranks and the digis), then
         // the stores: stores to the grouped copy could alias the input for the compiler,
@@ -597,7 +608,7 @@ __global__ __launch_bounds__(A_WG) void k_segment(LaunchArgs a) {
     // The small kernel's ticket starts at zero in every launch: the compaction kernel
     // of a finished launch resets it, and this reset also covers a launch whose later
     // kernels were never queued.
-    if (blockIdx.x == 0 && tid == 0) st_ag(&a.ctr[S_TICK], 0u);
+    if (blockIdx.x == 0 && tid == 0) st_ag(ticket(a), 0u);
 
     for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
         if (tid == 0) s_err = 0;
@@ -612,7 +623,7 @@ __global__ __launch_bounds__(A_WG) void k_segment(LaunchArgs a) {
         if ((reinterpret_cast<uintptr_t>(E.module) & 15u) == 0 && i0 + PER <= n) {
             uint4 v[PER / 8];                             // 16-byte loads, all in flight together
 #pragma unroll
-            for (u32 q = 0; q < PER / 8; ++q) v[q] = reinterpret_cast<const uint4*>(E.module + i0)[q];
+            for (u32 q = 0; q < PER / 8; ++q) v[q] = ((const uint4*)(E.module + i0))[q];
 #pragma unroll
             for (u32 q = 0; q < PER / 8; ++q) {
                 const u32 w[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
@@ -708,9 +719,9 @@ struct Item {
 // compiler then keeps them in scalar registers and branches on them uniformly).
 __device__ __forceinline__ u32 wave_uniform(u32 v) { return __builtin_amdgcn_readfirstlane(v); }
 template <typename T>
-__device__ __forceinline__ T* wave_uniform(T* p) {
+__device__ __forceinline__ T PXCL_G* wave_uniform(T PXCL_G* p) {
     const u64 x = reinterpret_cast<u64>(p);
-    return reinterpret_cast<T*>(u64(wave_uniform(u32(x))) | (u64(wave_uniform(u32(x >> 32))) << 32));
+    return (T PXCL_G*)(u64(wave_uniform(u32(x))) | (u64(wave_uniform(u32(x >> 32))) << 32));
 }
 __device__ __forceinline__ Item wave_uniform(const Item& I) {
     return Item{wave_uniform(I.e), wave_uniform(I.it), wave_uniform(I.st), wave_uniform(I.n), wave_uniform(I.mod),
@@ -1055,7 +1066,7 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
     // P9: per-digi cluster id (and, with fused hits, its weighted coordinates added
     // to its cluster's sums); clear the bitmap words used
     if (act) {
-        int32_t* od = E.o_digi;
+        int32_t* od = (int32_t*)E.o_digi;
         const u32* perm = perm_of(E, L);
         if (hits) {
 #pragma unroll
@@ -1138,7 +1149,7 @@ __device__ __forceinline__ void narrow_window(u32& lo, u32& hi, u64 ge, long lon
 
 __device__ __forceinline__ void module_range(const EventDesc& E, u32 n_modules, u32 key, u32 lane, u32& first,
                                              u32& end) {
-    const u16* mod = E.module;
+    const u16* mod = (const u16*)E.module;
     const u32 n = E.n;
     u32 lo0 = 0, hi0 = n, lo1 = 0, hi1 = n;       // each answer lies in [lo, hi]
     {
@@ -1343,7 +1354,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     const bool dyn = nstatic < total;             // tickets needed at all
     u32 round = 0;                                // round of the current module (>= nrounds: dynamic)
     u32 nv = total;                               // ticket of the next dynamic module (in flight)
-    if (dyn && nrounds == 1 && ((WAVE && lt == 0) || (!WAVE && tid == 0))) nv = atomicAdd(&a.ctr[S_TICK], STEP) + nstatic;
+    if (dyn && nrounds == 1 && ((WAVE && lt == 0) || (!WAVE && tid == 0))) nv = atomicAdd(ticket(a), STEP) + nstatic;
 
     while (base < total) {
         u32 nbase = total, nv2 = 0, ne = 0, nmod = 0;
@@ -1366,12 +1377,12 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
                 if constexpr (WAVE) {
                     nbase = snext ? base + per_round : __builtin_amdgcn_readfirstlane(nv);
                     nv2 = total;
-                    if (draw && lt == 0 && nbase < total) nv2 = atomicAdd(&a.ctr[S_TICK], 1u) + nstatic;
+                    if (draw && lt == 0 && nbase < total) nv2 = atomicAdd(ticket(a), 1u) + nstatic;
                     issue_entry();
                 } else if (tid == 0) {
                     const u32 nx = snext ? base + per_round : nv;
                     s.tick[1] = nx;
-                    nv2 = (draw && nx < total) ? atomicAdd(&a.ctr[S_TICK], STEP) + nstatic : total;
+                    nv2 = (draw && nx < total) ? atomicAdd(ticket(a), STEP) + nstatic : total;
                 }
             } else if (stage == 1) {
                 if constexpr (!WAVE) {
@@ -1471,10 +1482,10 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     constexpr u32 KW = MAX_RUNS / 32, KPT = (KW + BW - 1) / BW;
     constexpr u32 SPAN = UNR * BW;
     const u32 tid = threadIdx.x, n = I.n, st = I.st;
-    u32* cid = reinterpret_cast<u32*>(E.o_id) + st;       // per cluster: id (or -1 once cut)
-    u32* cch = reinterpret_cast<u32*>(E.o_charge) + st;   // per cluster: charge
-    u32* csz = reinterpret_cast<u32*>(E.o_size) + st;     // per cluster: size
-    int32_t* od = E.o_digi;
+    u32* cid = (u32*)E.o_id + st;       // per cluster: id (or -1 once cut)
+    u32* cch = (u32*)E.o_charge + st;   // per cluster: charge
+    u32* csz = (u32*)E.o_size + st;     // per cluster: size
+    int32_t* od = (int32_t*)E.o_digi;
     const u32* perm = perm_of(E, L);
     const bool hits = (E.flags & EF_HITS) != 0;
     u64* hs = ws_ptr<u64>(E, L.hsum);
@@ -1859,7 +1870,7 @@ __device__ __forceinline__ u32 kept_before(const u32* kept, u32 end, u32 lane) {
 __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
     const u32 tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
     const u32 k = num_events(a), M = a.n_modules, nblk = compact_blocks(M);
-    if (blockIdx.x == 0 && tid == 0) st_ag(&a.ctr[S_TICK], 0u);   // the small kernel has finished
+    if (blockIdx.x == 0 && tid == 0) st_ag(ticket(a), 0u);   // the small kernel has finished
     const u32 sp = compact_split(gridDim.x * C_WAVES, k * nblk);
     const u32 total = k * nblk * sp;
     for (u32 u = wave_uniform(xcd_order(blockIdx.x, gridDim.x) * C_WAVES + wv); u < total; u += gridDim.x * C_WAVES) {
@@ -1874,7 +1885,7 @@ __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
             // compacted, the lists and error bits stay for it, the host learns why
             if (b + 1 == nblk && part == 0 && lane == 0) {
                 ctl[CTL_DEFERRED] = 1u;
-                u32* hs = E.hstat;
+                u32* hs = (u32*)E.hstat;
                 st_sys(&hs[HS_ERR], ctl[CTL_ERR] | EB_DEFER);
                 st_sys(&hs[HS_NCL], 0u);
                 st_sys(&hs[HS_EPOCH], E.epoch);
@@ -1899,7 +1910,7 @@ __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
             st_ag(ctl + CTL_BIG, 0u);                      // the big kernels have run (other waves
             st_ag(ctl + CTL_SCR, 0u);                      // of the event may read them atomically)
             ctl[CTL_NCL] = ncl;
-            u32* hs = E.hstat;
+            u32* hs = (u32*)E.hstat;
             st_sys(&hs[HS_ERR], err);
             st_sys(&hs[HS_NCL], ncl);
             st_sys(&hs[HS_EPOCH], E.epoch);
@@ -1910,9 +1921,9 @@ __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
         const int32_t* tid_ = ws_ptr<const int32_t>(E, L.tid);
         const int32_t* tch = ws_ptr<const int32_t>(E, L.tcharge);
         const int32_t* tsz = ws_ptr<const int32_t>(E, L.tsize);
-        int32_t* oid = E.o_id;
-        int32_t* och = E.o_charge;
-        int32_t* osz = E.o_size;
+        int32_t* oid = (int32_t*)E.o_id;
+        int32_t* och = (int32_t*)E.o_charge;
+        int32_t* osz = (int32_t*)E.o_size;
         const bool hits = (E.flags & EF_HITS) != 0;
         u64* hsm = ws_ptr<u64>(E, L.hsum);
         float* hx = ws_ptr<float>(E, L.hit_x);
@@ -1992,9 +2003,9 @@ __global__ __launch_bounds__(H_WG) void k_hits(LaunchArgs a) {
         const u32 st = u32(r.first), nd = u32(r.end) - st;
         const u32 off = ws_ptr<const u32>(E, L.off)[mod];
         if (cnt > E.n || off > E.n - cnt || st > E.n || nd > E.n - st) continue;
-        const int32_t* ids = E.o_id + off;
-        const int32_t* chg = E.o_charge + off;
-        const int32_t* dcl = E.o_digi;
+        const int32_t* ids = (const int32_t*)E.o_id + off;
+        const int32_t* chg = (const int32_t*)E.o_charge + off;
+        const int32_t* dcl = (const int32_t*)E.o_digi;
         const u32* perm = perm_of(E, L);
         float* hx = ws_ptr<float>(E, L.hit_x) + off;
         float* hy = ws_ptr<float>(E, L.hit_y) + off;
