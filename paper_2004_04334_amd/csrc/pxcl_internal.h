@@ -41,7 +41,7 @@ constexpr u32 A_PER_N = 8, A_PER_W = 32;                    // narrow chunks for
                                                             // (fewer end-of-chunk atomics) else
 constexpr u32 C_WG = 256;                                   // compaction: a wave per module
 constexpr u32 K_SMALL = 8;                                  // digis per thread (small-module kernel)
-constexpr u32 B_WG = 512, K_BIG = 32;                       // big-module kernel
+constexpr u32 B_WG = 1024, K_BIG = 16;                      // big-module kernel
 constexpr u32 BIG_RCAP = B_WG * K_BIG;                      // 16384: larger modules use scratch mode
 constexpr u32 S_WG = 1024;                                  // scratch-mode kernel
 

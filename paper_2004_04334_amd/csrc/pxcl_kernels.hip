@@ -229,23 +229,6 @@ constexpr u32 NOPIX = 0xFFFFFFFFu;          // no pixel / no index
 // bitmap helpers (column-major: 5 words per column; bit b of word w is row
 // (w % 5)*32 + b of column w / 5)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ u32 fired(const u32* bm, u32 lin) { return (bm[lin >> 5] >> (lin & 31u)) & 1u; }
-
-// Bits of word w that start a vertical run (fired, with the pixel above not fired).
-__device__ __forceinline__ u32 run_starts(const u32* bm, u32 w) {
-    const u32 b = bm[w];
-    const u32 carry = (w % WPC) ? (bm[w - 1] >> 31) : 0u;
-    return b & ~((b << 1) | carry);
-}
-
-// Index of the vertical run containing fired pixel lin: run starts before word w
-// plus run starts in w at or below bit b, minus one.
-__device__ __forceinline__ u32 run_of(const u32* bm, const u16* rpre, u32 lin) {
-    const u32 w = lin >> 5, b = lin & 31u;
-    const u32 mask = (2u << b) - 1u;       // bits 0..b (b = 31 wraps to all ones)
-    return u32(rpre[w]) + __popc(run_starts(bm, w) & mask) - 1u;
-}
-
 // Union-find over runs in LDS: parent[x] <= x always; union hooks the larger root
 // under the smaller with atomicMin; find halves paths with plain stores, which only
 // ever point a node to one of its ancestors.  Both loops strictly decrease their
@@ -274,114 +257,138 @@ __device__ __forceinline__ void uf_unite(u32* par, u32 a, u32 b) {
     }
 }
 
-// Links (pairs of runs to unite) found by a group are listed in LDS first and united
-// afterwards, evenly over the group: a lane that finds several would otherwise unite
-// them one after another while the rest of its wave waits.  A link that does not fit
-// the list (capacity cap) is united at once.
-__device__ __forceinline__ void put_link(u32* list, u32 cap, u32* par, u32 pos, u32 a, u32 b) {
-    if (pos < cap) list[pos] = (a << 16) | b;
-    else uf_unite(par, a, b);
+// The same over the packed words of the register mode (RegModuleSmem::acc): the parent
+// of run x is the top 16 bits of word x, the rest is zero while runs are united.
+__device__ __forceinline__ u32* hi_word(u64* acc, u32 x) { return reinterpret_cast<u32*>(acc) + 2 * x + 1; }
+__device__ __forceinline__ u32 parent_of(u64* acc, u32 x) { return ld_wg(hi_word(acc, x)) >> 16; }
+__device__ __forceinline__ u32 find_packed(u64* acc, u32 x) {
+    for (u32 it = 0; it < 2 * MAX_RUNS; ++it) {
+        const u32 p = parent_of(acc, x);
+        if (p == x) return x;
+        const u32 g = parent_of(acc, p);
+        if (g == p) return p;
+        st_wg(hi_word(acc, x), g << 16);
+        x = g;
+    }
+    return x;
+}
+__device__ __forceinline__ void unite_packed(u64* acc, u32 a, u32 b) {
+    for (u32 it = 0; it < 2 * MAX_RUNS; ++it) {
+        a = find_packed(acc, a);
+        b = find_packed(acc, b);
+        if (a == b) return;
+        if (a < b) { const u32 t = a; a = b; b = t; }
+        const u32 old = __hip_atomic_fetch_min(hi_word(acc, a), b << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >> 16;
+        if (old == a) return;
+        a = old;
+    }
 }
 
 // Run index of row bit j of word w (fired), given the word's run starts s and the run
 // starts before it r0: runs are numbered in column-major order of their first pixel.
 __device__ __forceinline__ u32 run_at(u32 r0, u32 s, u32 j) { return r0 + __popc(s & ((2u << j) - 1u)) - 1u; }
 
-// Links between the runs of columns c and c+1 that meet rows 32k..32k+31 of them (both
-// columns hold a fired pixel, their run prefixes are set).  Rule B: every run start of
-// column c+1 is linked to the run of column c that holds the first fired pixel of the
-// start's rows -1..+1.  Rule A: every run start q of column c is linked to the run of
-// column c+1 holding the first fired pixel of rows q-1..q+1, when rule B does not
-// already make that link, which is when that pixel is at row q-1 and row q-2 is fired
-// in either column.  Every pair of touching runs X (column c+1), Y (column c) is linked
-// this way: if X's start lies within Y's rows widened by one, rule B links X to Y, or
-// to a run of column c ending right above X's start, and then Y starts just below
-// X's start, within one row of it, and rule A links Y to X; otherwise Y starts inside
-// X's rows widened by one, and rule A (or rule B for X, when X starts one row below
-// Y's start) links them.  Everything about the two columns comes from six bitmap
-// words and four run prefixes read once; only the unions touch the parents.
-__device__ __forceinline__ void link_word(u32* par, u32* list, u32 cap, u32* nlink, const u32* bm, const u16* rpre,
-                                          u32 c, u32 k) {
-    const u32 wa = c * WPC + k, wb = wa + WPC;
-    const bool has_prev = k > 0, has_next = k + 1 < WPC;
-    const u32 a = bm[wa], b = bm[wb];
-    const u32 pa = has_prev ? bm[wa - 1] : 0u, pb = has_prev ? bm[wb - 1] : 0u;   // rows 32k-32..32k-1
-    const u32 ap = pa >> 31, bp = pb >> 31;                                        // row 32k-1
-    const u32 an = has_next ? bm[wa + 1] & 1u : 0u;                                // row 32k+32
-    const u32 sa = a & ~((a << 1) | ap), sb = b & ~((b << 1) | bp);
-    // bit i of x_up / x_up2 / x_dn: the column fired at row i-1 / i-2 / i+1 of this word
-    const u32 a_up = (a << 1) | ap, a_dn = (a >> 1) | (an << 31), a_up2 = (a << 2) | (pa >> 30);
-    const u32 b_up = (b << 1) | bp, b_up2 = (b << 2) | (pb >> 30);
-    u32 ma = sa & b_up & (a_up2 | b_up2), mb = sb & (a_up | a | a_dn);
-    if (!(ma | mb)) return;
-    const u32 ra0 = rpre[wa], rb0 = rpre[wb];
-    const u32 ra1 = has_next ? rpre[wa + 1] : 0u;
-    // run of the other column (bits x, starts s, prefixes r0 / r1 of this word and the
-    // next) holding its first fired pixel among rows i-1, i, i+1
-    auto first_run = [](u32 i, u32 x, u32 x_up, u32 s, u32 r0, u32 r1) -> u32 {
-        if ((x_up >> i) & 1u) return i ? run_at(r0, s, i - 1) : r0 - 1u;   // row 32k-1: the last run before the word
-        if ((x >> i) & 1u) return run_at(r0, s, i);
-        return i < 31 ? run_at(r0, s, i + 1) : r1;   // row 32k+32 starts a run (row 32k+31 is empty)
-    };
-    u32 pos = atomicAdd(nlink, u32(__popc(mb) + __popc(ma)));
-    while (mb) {                                     // starts in column c+1
-        const u32 i = __builtin_ctz(mb);
-        mb &= mb - 1u;
-        put_link(list, cap, par, pos++, run_at(rb0, sb, i), first_run(i, a, a_up, sa, ra0, ra1));
+// Which runs of neighbouring columns are united.  Rule B: every run start of column c+1
+// is linked to the run of column c that holds the first fired pixel of the start's rows
+// -1..+1.  Rule A: every run start q of column c is linked to the run of column c+1
+// holding the first fired pixel of rows q-1..q+1, when rule B does not already make that
+// link, which is when that pixel is at row q-1 and row q-2 is fired in either column.
+// Every pair of touching runs X (column c+1), Y (column c) is linked this way: if X's
+// start lies within Y's rows widened by one, rule B links X to Y, or to a run of column c
+// ending right above X's start, and then Y starts just below X's start, within one row of
+// it, and rule A links Y to X; otherwise Y starts inside X's rows widened by one, and
+// rule A (or rule B for X, when X starts one row below Y's start) links them.  Runs are
+// numbered in column-major order of their first pixel, so rule B links a run to a smaller
+// one, and each run has at most one such link.
+
+// The bitmap lies between words that stay zero, so that the columns on either side of
+// the first and the last one read as not fired.
+constexpr u32 BM_FRONT = WPC, BM_WORDS = BM_FRONT + WORDS + WPC + 3;
+
+// Run numbers of a column: its first run in the low 16 bits, then one byte per bitmap
+// word: the runs that start in the column before the word, less one when bit 0 of the
+// word continues a run of the word above.  The run of row r (fired, in word k with bits b)
+// is then first + byte k + the number of bits of b & ~(b << 1) up to r, less one: a lookup
+// needs the entry and the one bitmap word.
+__device__ __forceinline__ u32 runs_before(u64 e, u32 k) { return u32(e & 0xFFFFu) + (u32(e >> (16 + 8 * k)) & 255u); }
+__device__ __forceinline__ u32 run_number(u64 e, u32 k, u32 word, u32 row) {
+    return runs_before(e, k) + __popc(word & ~(word << 1) & ((2u << (row & 31u)) - 1u)) - 1u;
+}
+
+// Entry of column c but for its first run, and its number of runs.
+__device__ __forceinline__ u64 col_entry(const u32* bm, u32 c, u32& n_runs) {
+    u64 e = 0ull;
+    u32 above = 0, runs = 0;
+#pragma unroll
+    for (u32 k = 0; k < WPC; ++k) {
+        const u32 b = bm[BM_FRONT + c * WPC + k], cont = b & above;
+        e |= u64(runs - cont) << (16 + 8 * k);
+        runs += __popc(b & ~(b << 1)) - cont;
+        above = b >> 31;
     }
-    while (ma) {                                     // starts in column c (row i-1 fired in c+1)
-        const u32 i = __builtin_ctz(ma);
-        ma &= ma - 1u;
-        put_link(list, cap, par, pos++, run_at(ra0, sa, i), i ? run_at(rb0, sb, i - 1) : rb0 - 1u);
+    n_runs = runs;
+    return e;
+}
+
+// Rows 32k..32k+31 of a column: bits, the rows above (row 32k-1 in bit 31) and below (row
+// 32k+32 in bit 0), run starts, and the runs before the word.
+struct ColWord {
+    u32 b, above, below, st, r0;
+};
+__device__ __forceinline__ ColWord col_word(const u32* bm, const u64* col, u32 c, u32 k) {   // col[c + 1]: column c's entry
+    const u32* w = &bm[BM_FRONT + c * WPC + k];
+    ColWord x;
+    x.b = w[0];
+    x.above = k ? *(w - 1) : 0u;
+    x.below = k + 1 < WPC ? w[1] : 0u;
+    x.st = x.b & ~((x.b << 1) | (x.above >> 31));
+    x.r0 = runs_before(col[c + 1], k) + (x.b & (x.above >> 31));
+    return x;
+}
+
+// first(run, parent) for every run that starts in word k of column c: rule B's run, or the
+// run itself.
+template <typename F>
+__device__ __forceinline__ void word_parents(const u32* bm, const u64* col, u32 c, u32 k, F first) {
+    const ColWord x = col_word(bm, col, c, k);
+    if (!x.st) return;
+    u32 run = x.r0, m = x.st;
+    ColWord l{};
+    if (c) l = col_word(bm, col, c - 1, k);
+    const u32 up = (l.b << 1) | (l.above >> 31), dn = (l.b >> 1) | (l.below << 31), touch = up | l.b | dn;
+    const u32 next = c ? runs_before(col[c], k + 1 < WPC ? k + 1 : k) : 0u;   // the run of row 32k+32 (if it starts there)
+    while (m) {
+        const u32 i = __builtin_ctz(m);
+        m &= m - 1u;
+        u32 parent = run;
+        if ((touch >> i) & 1u) {
+            if ((up >> i) & 1u) parent = i ? run_at(l.r0, l.st, i - 1) : l.r0 - 1u;
+            else if ((l.b >> i) & 1u) parent = run_at(l.r0, l.st, i);
+            else parent = i < 31 ? run_at(l.r0, l.st, i + 1) : next;
+        }
+        first(run, parent);
+        ++run;
     }
 }
 
-// The same two rules for one column pair (c, c+1) by one wave, a lane per row (rows
-// lane, lane + 64, lane + 128): the scratch mode's walk over the columns.  The ten
-// words of the two columns and their run prefixes are read once per step (load_pair,
-// issued one step ahead), the rest is register work and the unions.
-struct ColPair {
-    u32 A[WPC], B[WPC], RA[WPC], RB[WPC];
-};
-__device__ __forceinline__ void load_pair(ColPair& P, const u32* bm, const u16* rpre, u32 c) {
-#pragma unroll
-    for (u32 k = 0; k < WPC; ++k) {
-        P.A[k] = bm[c * WPC + k];
-        P.B[k] = bm[(c + 1) * WPC + k];
-        P.RA[k] = rpre[c * WPC + k];
-        P.RB[k] = rpre[(c + 1) * WPC + k];
-    }
-}
-__device__ __forceinline__ u32 sel5(const u32 (&v)[WPC], u32 k) {
-    return k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[2] : k == 3 ? v[3] : v[4];
-}
-__device__ __forceinline__ void link_pair(u32* par, const ColPair& P, u32 lane) {
-    u32 any = 0;
-#pragma unroll
-    for (u32 k = 0; k < WPC; ++k) any |= P.A[k] | P.B[k];
-    if (!any) return;                                // the same for the whole wave
-    u32 SA[WPC], SB[WPC];
-#pragma unroll
-    for (u32 k = 0; k < WPC; ++k) {
-        SA[k] = P.A[k] & ~((P.A[k] << 1) | (k ? P.A[k - 1] >> 31 : 0u));
-        SB[k] = P.B[k] & ~((P.B[k] << 1) | (k ? P.B[k - 1] >> 31 : 0u));
-    }
-    auto bit = [](const u32 (&W)[WPC], u32 row) -> u32 {   // fired at row (any u32: out of range = 0)
-        return row < ROWS ? (sel5(W, row >> 5) >> (row & 31u)) & 1u : 0u;
-    };
-    auto run = [](const u32 (&S)[WPC], const u32 (&R)[WPC], u32 row) -> u32 {
-        return run_at(sel5(R, row >> 5), sel5(S, row >> 5), row & 31u);
-    };
-#pragma unroll
-    for (u32 j = 0; j < 3; ++j) {
-        const u32 p = lane + 64u * j;
-        if (p >= ROWS) break;
-        if (bit(SB, p)) {                            // rule B
-            const u32 f = bit(P.A, p - 1u) ? p - 1u : bit(P.A, p) ? p : bit(P.A, p + 1u) ? p + 1u : NOPIX;
-            if (f != NOPIX) uf_unite(par, run(SB, P.RB, p), run(SA, P.RA, f));
-        }
-        if (bit(SA, p) && bit(P.B, p - 1u) && (bit(P.A, p - 2u) | bit(P.B, p - 2u)))   // rule A
-            uf_unite(par, run(SA, P.RA, p), run(SB, P.RB, p - 1u));
+// link(run, run of column c + 1) for every rule A link of the runs that start in word k
+// of column c.
+template <typename F>
+__device__ __forceinline__ void word_links(const u32* bm, const u64* col, u32 c, u32 k, F link) {
+    if (c + 1 >= COLS) return;
+    const u32* w = &bm[BM_FRONT + c * WPC + k];
+    const u32 a = w[0], b = w[WPC];
+    if (!a) return;
+    const u32 pa = k ? *(w - 1) : 0u, pb = k ? w[WPC - 1] : 0u;      // rows 32k-32..32k-1
+    const u32 sa = a & ~((a << 1) | (pa >> 31));
+    u32 m = sa & ((b << 1) | (pb >> 31)) & (((a << 2) | (pa >> 30)) | ((b << 2) | (pb >> 30)));
+    if (!m) return;
+    const u32 ra0 = runs_before(col[c + 1], k) + (a & (pa >> 31)), rb0 = runs_before(col[c + 2], k) + (b & (pb >> 31));
+    const u32 sb = b & ~((b << 1) | (pb >> 31));
+    while (m) {
+        const u32 i = __builtin_ctz(m);
+        m &= m - 1u;
+        link(run_at(ra0, sa, i), i ? run_at(rb0, sb, i - 1) : rb0 - 1u);
     }
 }
 
@@ -697,17 +704,17 @@ constexpr u32 CMW = (COLS + 31) / 32;   // words of a per-module column mask
 template <u32 G, u32 K>
 struct RegModuleSmem {
     static constexpr u32 RCAP = G * K, KBW = RCAP / 32;
-    u32 bm[WORDS];     // fired-pixel bitmap (clear between modules)
+    u32 bm[BM_WORDS];  // fired-pixel bitmap (clear between modules)
     u32 cm[CMW];       // columns holding a fired pixel (clear between modules)
-    u64 acc[RCAP];     // union-find parents (u32, first half) and the links found (u32,
-                       // second half), then charge | size << 44
+    u64 col[COLS + 2]; // entry c+1: column c's run numbers (see col_entry)
+    u64 acc[RCAP];     // per run: parent (16 bits) | size (16) | charge (32), charge and
+                       // size at the roots only; then, at the roots, first pixel (17) |
+                       // size (15) | charge (32)
     u32 kb[KBW];       // kept-root bits over run index
-    u16 rpre[WORDS];   // run starts before each word
     u16 kpre[KBW];     // kept roots before each kb word
     u32 wsum[G / 64];
-    u32 nlink;         // links found (entries of the link list)
+    u32 nlink;         // some pair of runs is left to unite
 };
-
 
 // A module as a group sees it.
 struct Item {
@@ -754,78 +761,74 @@ __device__ __forceinline__ EventDesc wave_uniform(const EventDesc& E) {
 // Issue the loads of the module's digis j = lt + q*G < n: row and column packed in
 // one register (row | col << 16, half-word loads into each half), adc in another; the
 // values are only used when the module is clustered, so the loads stay in flight
-// meanwhile.  With few slots per thread, slots past the module's end are not
-// loaded; with many (the big-module kernel) every slot loads a digi of the module
-// (unconditional loads keep that kernel's register allocation within bounds).
+// meanwhile.
 template <u32 G, u32 K>
 __device__ __forceinline__ void fetch_digis(const EventDesc& E, const Item& I, u32 lt, u32* RC, u32* A) {
 #pragma unroll
     for (u32 q = 0; q < K; ++q) {
         const u32 j = lt + q * G;
-        if constexpr (K <= 8) {
-            RC[q] = A[q] = 0u;
-            if (q * G < I.n && j < I.n) {
-                RC[q] = u32(E.row[I.st + j]) | (u32(E.col[I.st + j]) << 16);
-                A[q] = E.adc[I.st + j];
-            }
-        } else {
-            const u32 i = I.st + (j < I.n ? j : 0u);     // always inside the module
-            RC[q] = u32(E.row[i]) | (u32(E.col[i]) << 16);
-            A[q] = E.adc[i];
+        RC[q] = A[q] = 0u;
+        if (q * G < I.n && j < I.n) {
+            RC[q] = u32(E.row[I.st + j]) | (u32(E.col[I.st + j]) << 16);
+            A[q] = E.adc[I.st + j];
         }
     }
 }
 
-// f(q) for the digi slots q < nq (nq uniform over the group).  With few slots per
-// thread the loop is not unrolled, so a large body appears once in the code (the
-// register arrays it indexes with the uniform q stay in registers).
-template <u32 K, typename F>
+// f(q) for the digi slots q < nq (nq uniform over the group), in steps of U that the
+// compiler may interleave (f must do nothing for a slot at or above nq).  The loop over the
+// steps is not unrolled, so a large body appears once in the code (the register arrays it
+// indexes with the uniform q stay in registers).
+template <u32 K, u32 U, typename F>
 __device__ __forceinline__ void for_slots(u32 nq, F f) {
-    if constexpr (K <= 8) {
+    static_assert(K % U == 0, "whole steps");
 #pragma unroll 1
-        for (u32 q = 0; q < nq; ++q) f(q);
-    } else {
+    for (u32 q = 0; q < nq; q += U)
 #pragma unroll
-        for (u32 q = 0; q < K; ++q)
-            if (q < nq) f(q);
-    }
+        for (u32 u = 0; u < U; ++u) f(q + u);
 }
 
 // Cluster module I (n <= G*K) whose raw digis are in RC/A (fetch_digis).  Every
-// thread of the group calls it; with G > 64 all groups of the workgroup call it
-// together.  `mid(stage)` runs at the end of phase 1, at the start of phase 3, at
-// the end of phase 5 and at the end of phase 8 (the next module's prefetch).
-template <u32 G, u32 K, typename Mid>
+// thread of the group calls it; with G > 64 all groups of the workgroup (SOLE: there is
+// one) call it together.  `mid(stage)` runs at the end of phase 1, at the start of phase 3 and after
+// phase 5 (the next module's prefetch).
+//
+// What bounds it is the chain of phases, each an LDS latency or two behind a barrier, so
+// the phases are few (8 barriers) and the LDS reads of a phase do not depend on each other:
+//   1  bitmap
+//   2  run numbers of the columns
+//   3  every digi reads the four rows around it in three columns (three pairs of adjacent
+//      words) and the three columns' entries, all at once, and finds its run; a digi that
+//      starts a run stores the run's parent: the run rule B links it to, or itself (a
+//      plain store: no other link decides the first parent)
+//   4  only if some run has a rule A link: those unions
+//   5  root of every digi's run, charge and size into the root's word
+//   6  cut, one bit per kept root
+//   7  outputs
+template <u32 G, u32 K, bool SOLE, typename Mid>
 __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDesc& E, const EvLayout& L,
                                              const Item& I, RegModuleSmem<G, K>& gp, u32 lt, const u32* RC,
                                              const u32* A, Mid mid) {
-    static_assert(G * K <= 65536, "run indices are kept in 16 bits");
+    static_assert(G * K <= 16384, "sizes of up to 15 bits, run numbers of up to 16");
     constexpr u32 KBW = G * K / 32, CPT = (COLS + G - 1) / G;
-    // dense modules (the big-module kernel): unions per (column, word) of the bitmap
-    // and roots per run; sparse ones: unions and roots per digi
-    constexpr bool WORD_LINKS = K > 8;
     const bool hits = (E.flags & EF_HITS) != 0;
     u64* hs = ws_ptr<u64>(E, L.hsum);
-    u32* par = reinterpret_cast<u32*>(gp.acc);
     const bool act = I.ok;
     const u32 nq = act ? min((I.n + G - 1) / G, K) : 0u;   // slots that may hold a digi
-    u32 err = 0;
-    // LIN: linear pixel index or NOPIX; AR: adc in the low 16 bits, then run / root
-    u32 LIN[K], AR[K];
-    // P1: insert the module's digis into the bitmap
+    u32 err = 0, valid = 0, starts = 0;                    // bit q: slot q holds a pixel, starts its run
+    auto has = [&](u32 mask, u32 q) { return ((mask >> q) & 1u) != 0; };
+    // 1: the module's digis into the bitmap
+    if (lt == 0) gp.nlink = 0u;
+    for (u32 w = lt; w < KBW; w += G) gp.kb[w] = 0u;
 #pragma unroll
     for (u32 q = 0; q < K; ++q) {
-        const u32 j = lt + q * G;
-        LIN[q] = NOPIX;
-        AR[q] = A[q] & 0xFFFFu;
-        if (q < nq && j < I.n) {
+        if (q < nq && lt + q * G < I.n) {
             const u32 rq = RC[q] & 0xFFFFu, cq = RC[q] >> 16;
             if (rq < ROWS && cq < COLS) {
-                const u32 lin = cq * ROWS + rq;
-                const u32 bit = 1u << (lin & 31u);
-                if (atomicOr(&gp.bm[lin >> 5], bit) & bit) err |= EB_DUP;
+                const u32 bit = 1u << (rq & 31u);
+                if (atomicOr(&gp.bm[BM_FRONT + cq * WPC + (rq >> 5)], bit) & bit) err |= EB_DUP;
                 atomicOr(&gp.cm[cq >> 5], 1u << (cq & 31u));
-                LIN[q] = lin;
+                valid |= 1u << q;
             } else {
                 err |= EB_RANGE;
             }
@@ -833,263 +836,182 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
     }
     mid(0);
     gsync<G>();
-    // P2: run starts per word of the columns holding a fired pixel (the only words
-    // whose run index is ever asked for), prefix over them in column order; parents.
-    // A thread takes CPT consecutive columns; per column the five word counts are kept
-    // packed, 6 bits each.
-    u32 nruns = 0;
+    // 2: run starts per word of the columns holding a fired pixel (the only ones whose run
+    // numbers are ever asked for), prefix over them in column order.  A thread takes CPT
+    // consecutive columns.
     {
-        u32 pk[CPT];
-        u32 cnt = 0;
+        u64 ent[CPT];
+        u32 cnt = 0, sum[CPT];
         const u32 c0 = lt * CPT;
 #pragma unroll
         for (u32 i = 0; i < CPT; ++i) {
             const u32 c = c0 + i;
-            pk[i] = 0u;
+            ent[i] = 0ull;
+            sum[i] = NOPIX;
             if (act && c < COLS && ((gp.cm[c >> 5] >> (c & 31u)) & 1u)) {
-#pragma unroll
-                for (u32 k = 0; k < WPC; ++k) {
-                    const u32 v = __popc(run_starts(gp.bm, c * WPC + k));
-                    pk[i] |= v << (6 * k);
-                    cnt += v;
-                }
-                pk[i] |= 1u << 31;                       // column fired
+                ent[i] = col_entry(gp.bm, c, sum[i]);
+                cnt += sum[i];
             }
         }
-        const u32 ex = group_excl_scan<G>(cnt, lt, gp.wsum, nruns);
-        u32 run = ex;
-#pragma unroll
-        for (u32 i = 0; i < CPT; ++i) {
-            if (pk[i] >> 31) {
-                const u32 c = c0 + i;
-#pragma unroll
-                for (u32 k = 0; k < WPC; ++k) {
-                    gp.rpre[c * WPC + k] = u16(run);
-                    run += (pk[i] >> (6 * k)) & 63u;
-                }
-            }
+        const u32 inc = wave_incl_scan(cnt);
+        u32 run = inc - cnt;
+        if constexpr (G > 64) {
+            if ((lt & 63u) == 63u) gp.wsum[lt >> 6] = inc;
+            gsync<G>();
+            for (u32 i = 0; i < G / 64; ++i) run += i < (lt >> 6) ? gp.wsum[i] : 0u;
         }
+#pragma unroll
+        for (u32 i = 0; i < CPT; ++i)
+            if (sum[i] != NOPIX) {
+                gp.col[c0 + i + 1] = ent[i] | run;
+                run += sum[i];
+            }
     }
-    if (act)
-        for (u32 r = lt; r < nruns; r += G) par[r] = r;
-    if (lt == 0) gp.nlink = 0u;
     gsync<G>();
     mid(1);
-    u32 starts = 0;
-    constexpr u32 LCAPL = G * K;                     // link list capacity
-    u32* links = reinterpret_cast<u32*>(gp.acc) + G * K;
-    // unite the listed links, evenly over the group
-    auto unite_links = [&]() {
-        gsync<G>();
-        if (act) {
-            const u32 nl = min(ld_wg(&gp.nlink), LCAPL);
-            for (u32 t = lt; t < nl; t += G) {
-                const u32 l = links[t];
-                uf_unite(par, l >> 16, l & 0xFFFFu);
-            }
+    // 3: every digi's run (X: the run, above it the run a rule A link goes to), first parents
+    u32 X[K];
+    u32 link = 0;                                          // bit q: slot q has a rule A link
+    for_slots<K, 2>(nq, [&](u32 q) {
+        X[q] = 0u;
+        if (!has(valid, q)) return;
+        const u32 row = RC[q] & 0xFFFFu, c = RC[q] >> 16;
+        // rows s..s+3 of the columns c-1, c, c+1 lie in two adjacent words each
+        const u32 s = row >= 2 ? row - 2 : 0u, ks = s >> 5;
+        const u32* w = &gp.bm[BM_FRONT + c * WPC + ks - WPC];
+        const u32 l0 = w[0], l1 = w[1], m0 = w[WPC], m1 = w[WPC + 1], r0 = w[2 * WPC], r1 = w[2 * WPC + 1];
+        const u64 el = gp.col[c], em = gp.col[c + 1], er = gp.col[c + 2];
+        // bit i: row - 2 + i fired (above the first row and below the last one: not)
+        const u32 up = row >= 2 ? 0u : 2u - row, mask = row + 1 < ROWS ? 15u : 7u;
+        auto window = [&](u32 lo, u32 hi) { return (u32(((u64(hi) << 32) | lo) >> (s & 31u)) << up) & mask; };
+        const u32 wl = window(l0, l1), wm = window(m0, m1), wr = window(r0, r1);
+        const u32 kr = row >> 5;
+        const u32 r = run_number(em, kr, kr == ks ? m0 : m1, row);
+        X[q] = r;
+        if (wm & 2u) return;                               // not the first pixel of its run
+        starts |= 1u << q;
+        u32 parent = r;
+        if (wl & 14u) {                                    // rule B
+            const u32 f = row - 1u + __builtin_ctz((wl >> 1) & 7u), kf = f >> 5;
+            parent = run_number(el, kf, kf == ks ? l0 : l1, f);
         }
-    };
-    if constexpr (WORD_LINKS) {
-        // P3: links between adjacent fired columns, one (column, word) unit at a time
-        if (act)
-            for (u32 u = lt; u < (COLS - 1) * WPC; u += G) {
-                const u32 c = u / WPC, k = u - c * WPC;
-                if (((gp.cm[c >> 5] >> (c & 31u)) & 1u) && ((gp.cm[(c + 1) >> 5] >> ((c + 1) & 31u)) & 1u))
-                    link_word(par, links, LCAPL, &gp.nlink, gp.bm, gp.rpre, c, k);
-            }
-        unite_links();
-        gsync<G>();
-        // P4: every run points at its root (walks only read; each store writes a root,
-        // so a walk through a stored entry still ends at the same root)
-        if (act)
-            for (u32 r = lt; r < nruns; r += G) {
-                u32 x = ld_wg(&par[r]);
-                for (u32 it = 0; it < MAX_RUNS; ++it) {
-                    const u32 y = ld_wg(&par[x]);
-                    if (y == x) break;
-                    x = y;
-                }
-                st_wg(&par[r], x);
-            }
-        gsync<G>();
-        // each digi's run and root; the digi that starts its root's run speaks for the cluster
-        u32 RN[K];
-#pragma unroll
-        for (u32 q = 0; q < K; ++q) RN[q] = (q < nq && LIN[q] != NOPIX) ? run_of(gp.bm, gp.rpre, LIN[q]) : 0u;
-#pragma unroll
-        for (u32 q = 0; q < K; ++q)
-            if (q < nq && LIN[q] != NOPIX) {
-                const u32 lin = LIN[q], root = ld_wg(&par[RN[q]]);
-                if (root == RN[q] && !((lin % ROWS) > 0 && fired(gp.bm, lin - 1))) starts |= 1u << q;
-                AR[q] = (AR[q] & 0xFFFFu) | (root << 16);
-            }
-        gsync<G>();
-    } else {
-        // P3: the two rules of link_word, from the digi that starts each run: rule B
-        // links the run to the run of the column on its left holding the first fired
-        // pixel of rows -1..+1, rule A to the run of the column on its right at row -1
-        // when row -2 is fired in either column.
-        u32 RS = 0;                                  // slots whose digi starts its run
-        const u32 lane = lt & 63u;
-        const u64 below = (1ull << lane) - 1ull;
-        for_slots<K>(nq, [&](u32 q) {                // every lane of the group runs every slot
-            const u32 lin = LIN[q];
-            u32 r = 0, ob = NOPIX, oa = NOPIX;       // the run, its links' other runs
-            if (lin != NOPIX) {
-                const u32 col = lin / ROWS, row = lin - col * ROWS;
-                // every bitmap word the rules look at, read at once: rows -2..+1 of
-                // this column and of the columns on either side (clamped into the
-                // module; out-of-module rows and columns are masked off below)
-                const u32 lo = row >= 2 ? lin - 2 : lin - row, hi = row + 1 < ROWS ? lin + 1 : lin;
-                const u32 lcol = col > 0 ? ROWS : 0u, rcol = col + 1 < COLS ? ROWS : 0u;
-                const u32 w0 = lo >> 5, w1 = hi >> 5;                      // this column
-                const u32 l0 = (lo - lcol) >> 5, l1 = (hi - lcol) >> 5;    // left
-                const u32 r0 = (lo + rcol) >> 5, r1 = (hi + rcol) >> 5;    // right
-                const u32 bw0 = gp.bm[w0], bw1 = gp.bm[w1], bl0 = gp.bm[l0], bl1 = gp.bm[l1];
-                const u32 br0 = gp.bm[r0], br1 = gp.bm[r1];
-                const u32 bp = gp.bm[w0 ? w0 - 1 : 0u], rp = gp.rpre[lin >> 5];
-                // fired(pixel at this column's row `rr`, column offset d in {-1, 0, +1})
-                auto at = [&](u32 rr, int d) -> u32 {
-                    if (rr >= ROWS) return 0u;
-                    if ((d < 0 && !col) || (d > 0 && col + 1 >= COLS)) return 0u;
-                    const u32 x = lin - row + rr + (d < 0 ? 0u - ROWS : d > 0 ? ROWS : 0u);
-                    const u32 base = d < 0 ? l0 : d > 0 ? r0 : w0;
-                    const u32 word = (x >> 5) == base ? (d < 0 ? bl0 : d > 0 ? br0 : bw0) : (d < 0 ? bl1 : d > 0 ? br1 : bw1);
-                    return (word >> (x & 31u)) & 1u;
-                };
-                {   // own run: run starts in this word up to this row
-                    const u32 w = lin >> 5, b = lin & 31u;
-                    const u32 bwd = (w == w0) ? bw0 : bw1;
-                    const u32 carry = (w % WPC) ? (((w == w0) ? bp : bw0) >> 31) : 0u;
-                    const u32 st = bwd & ~((bwd << 1) | carry);
-                    r = u32(rp) + __popc(st & ((2u << b) - 1u)) - 1u;
-                }
-                AR[q] |= r << 16;
-                if (!at(row - 1u, 0)) {                      // the digi starts its run
-                    RS |= 1u << q;
-                    const u32 f = at(row - 1u, -1) ? row - 1u : at(row, -1) ? row : at(row + 1u, -1) ? row + 1u : NOPIX;
-                    const bool la = at(row - 1u, 1) && (at(row - 2u, 0) || at(row - 2u, 1));
-                    // run lookups (independent of each other)
-                    if (f != NOPIX) ob = run_of(gp.bm, gp.rpre, lin - row + f - ROWS);
-                    if (la) oa = run_of(gp.bm, gp.rpre, lin + ROWS - 1u);
-                }
-            }
-            // places in the list: one LDS atomic per wave
-            const u64 mb = __ballot(ob != NOPIX), ma = __ballot(oa != NOPIX);
-            const u32 nb = u32(__popcll(mb)), na = u32(__popcll(ma));
-            if (nb + na) {
-                u32 base = 0;
-                if (lane == 0) base = atomicAdd(&gp.nlink, nb + na);
-                base = __shfl(base, 0, 64);
-                if (ob != NOPIX) put_link(links, LCAPL, par, base + u32(__popcll(mb & below)), r, ob);
-                if (oa != NOPIX) put_link(links, LCAPL, par, base + nb + u32(__popcll(ma & below)), r, oa);
-            }
-        });
-        unite_links();
-        gsync<G>();
-        // P4: every run points at its root (read-only walks, each store a root), then
-        // each digi's root in one load; the digi that starts its root's run speaks for
-        // the cluster
-        if (act)
-            for (u32 r = lt; r < nruns; r += G) {
-                u32 x = ld_wg(&par[r]);
-                for (u32 it = 0; it < MAX_RUNS; ++it) {
-                    const u32 y = ld_wg(&par[x]);
-                    if (y == x) break;
-                    x = y;
-                }
-                st_wg(&par[r], x);
-            }
-        gsync<G>();
-#pragma unroll
-        for (u32 q = 0; q < K; ++q)
-            if (q < nq && LIN[q] != NOPIX) {
-                const u32 run = AR[q] >> 16, root = ld_wg(&par[run]);
-                if (root == run && ((RS >> q) & 1u)) starts |= 1u << q;
-                AR[q] = (AR[q] & 0xFFFFu) | (root << 16);
-            }
-        gsync<G>();
-    }
-    if (act) {
-        for (u32 r = lt; r < nruns; r += G) gp.acc[r] = 0ull;
-        for (u32 w = lt; w < KBW; w += G) gp.kb[w] = 0u;
-    }
+        gp.acc[r] = u64(parent) << 48;
+        if ((wr & 2u) && ((wm | wr) & 1u)) {               // rule A
+            const u32 f = row - 1u, kf = f >> 5;
+            X[q] |= run_number(er, kf, kf == ks ? r0 : r1, f) << 16;
+            link |= 1u << q;
+        }
+    });
+    if (link) st_wg(&gp.nlink, 1u);
     gsync<G>();
-    // P5: charge and size per root
+    // 4: rule A's unions (groups that share the workgroup's barrier all take it)
+    const bool unions = ld_wg(&gp.nlink) != 0;
+    if (unions) {
+#pragma unroll
+        for (u32 q = 0; q < K; ++q)
+            if (has(link, q)) unite_packed(gp.acc, X[q] & 0xFFFFu, X[q] >> 16);
+    }
+    if ((G > 64 && !SOLE) || unions) gsync<G>();
+    // 5: roots (the walks of all slots step together; each store points a run to one of its
+    // ancestors), then charge and size per root.  Sums touch the low 48 bits of roots only,
+    // walks read the parents and write those of other runs.
+#pragma unroll
+    for (u32 q = 0; q < K; ++q) X[q] &= 0xFFFFu;
+    u32 todo = valid;
+    for (u32 it = 0; todo && it < 2 * MAX_RUNS; ++it) {
+        u32 P[K];
+#pragma unroll
+        for (u32 q = 0; q < K; ++q)
+            if (q < nq && has(todo, q)) P[q] = parent_of(gp.acc, X[q]);
+#pragma unroll
+        for (u32 q = 0; q < K; ++q)
+            if (q < nq && has(todo, q)) {
+                const u32 g = parent_of(gp.acc, P[q]);
+                if (P[q] != X[q]) starts &= ~(1u << q);    // now: the digi starts its cluster
+                if (g == P[q]) todo &= ~(1u << q);
+                else st_wg(hi_word(gp.acc, X[q]), g << 16);
+                X[q] = g;
+            }
+    }
 #pragma unroll
     for (u32 q = 0; q < K; ++q)
-        if (q < nq && LIN[q] != NOPIX) atomicAdd(&gp.acc[AR[q] >> 16], (1ull << 44) | u64(AR[q] & 0xFFFFu));
+        if (q < nq && has(valid, q)) {
+            atomicAdd(&gp.acc[X[q]], (1ull << 32) | u64(A[q] & 0xFFFFu));
+        }
     mid(2);
     gsync<G>();
-    // P6: charge cut, one bit per kept root
+    // 6: charge cut, one bit per kept root; its word's upper half becomes the first pixel
+    // and the size
 #pragma unroll
     for (u32 q = 0; q < K; ++q)
-        if (q < nq && (starts & (1u << q))) {
-            const u32 r = AR[q] >> 16;
-            if (u32(gp.acc[r]) >= a.charge_cut) atomicOr(&gp.kb[r >> 5], 1u << (r & 31u));
+        if (q < nq && has(starts, q)) {
+            const u32 r = X[q];
+            const u64 v = gp.acc[r];
+            const u32 lin = (RC[q] >> 16) * ROWS + (RC[q] & 0xFFFFu);
+            if (u32(v) >= a.charge_cut) atomicOr(&gp.kb[r >> 5], 1u << (r & 31u));
+            st_wg(hi_word(gp.acc, r), (lin << 15) | (u32(v >> 32) & 0x7FFFu));
         }
     gsync<G>();
-    // P7: kept roots before each kb word
-    u32 Kc;
-    {
-        const u32 c = (act && lt < KBW) ? __popc(gp.kb[lt]) : 0u;
-        const u32 ex = group_excl_scan<G>(c, lt, gp.wsum, Kc);
-        if (act && lt < KBW) gp.kpre[lt] = u16(ex);
-    }
-    gsync<G>();
-    // P8: kept clusters -> staging records at [st + position in the module]
+    // 7: kept roots before each kb word (every wave writes all of them, the same values, and
+    // reads what it wrote), then the outputs: kept clusters -> staging records at
+    // [st + position in the module], per-digi cluster ids; with fused hits every kept digi's
+    // weighted coordinates go to its cluster's sums; the bitmap words used are cleared
     if (act) {
+        constexpr u32 KPL = (KBW + 63) / 64;               // kb words per lane
+        const u32 lane = lt & 63u;
+        u32 pc[KPL], cnt = 0;
+#pragma unroll
+        for (u32 i = 0; i < KPL; ++i) {
+            pc[i] = lane * KPL + i < KBW ? __popc(gp.kb[lane * KPL + i]) : 0u;
+            cnt += pc[i];
+        }
+        const u32 inc = wave_incl_scan(cnt);
+        u32 pre = inc - cnt;
+#pragma unroll
+        for (u32 i = 0; i < KPL; ++i) {
+            if (lane * KPL + i < KBW) __hip_atomic_store(&gp.kpre[lane * KPL + i], u16(pre), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            pre += pc[i];
+        }
+        gsync<64>();
+        if (lt == 63) ws_ptr<u32>(E, L.kept)[I.it] = inc;
+        auto position = [&](u32 r) {                       // of the kept root r in the module
+            return u32(__hip_atomic_load(&gp.kpre[r >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) +
+                   __popc(gp.kb[r >> 5] & ((1u << (r & 31u)) - 1u));
+        };
         int32_t* tid_ = ws_ptr<int32_t>(E, L.tid);
         int32_t* tch = ws_ptr<int32_t>(E, L.tcharge);
         int32_t* tsz = ws_ptr<int32_t>(E, L.tsize);
-        const u32 idbase = I.mod * PIX;
-#pragma unroll
-        for (u32 q = 0; q < K; ++q)
-            if (q < nq && (starts & (1u << q))) {
-                const u32 r = AR[q] >> 16;
-                const u64 v = gp.acc[r];
-                const u32 charge = u32(v), size = u32(v >> 44);
-                u32 id = NOPIX, pos = 0;
-                if (charge >= a.charge_cut) {
-                    pos = gp.kpre[r >> 5] + __popc(gp.kb[r >> 5] & ((1u << (r & 31u)) - 1u));
-                    id = idbase + LIN[q];
-                    tid_[I.st + pos] = int32_t(id);
-                    tch[I.st + pos] = int32_t(charge);
-                    tsz[I.st + pos] = int32_t(size);
-                }
-                gp.acc[r] = u64(id) | (u64(pos) << 32);        // id (or -1) and record for P9
-            }
-        if (lt == 0) ws_ptr<u32>(E, L.kept)[I.it] = Kc;
-    }
-    mid(3);
-    gsync<G>();
-    // P9: per-digi cluster id (and, with fused hits, its weighted coordinates added
-    // to its cluster's sums); clear the bitmap words used
-    if (act) {
         int32_t* od = (int32_t*)E.o_digi;
         const u32* perm = perm_of(E, L);
-        if (hits) {
-#pragma unroll
-            for (u32 q = 0; q < K; ++q)
-                if (q < nq && LIN[q] != NOPIX) {
-                    const u64 v = gp.acc[AR[q] >> 16];
-                    if (u32(v) != NOPIX) {
-                        const u32 p = I.st + u32(v >> 32), lin = LIN[q], col = lin / ROWS;
-                        const u64 w = AR[q] & 0xFFFFu;
-                        atomicAdd(&hs[2 * p], w * col);
-                        atomicAdd(&hs[2 * p + 1], w * (lin - col * ROWS));
-                    }
-                }
-        }
+        const u32 idbase = I.mod * PIX;
 #pragma unroll
         for (u32 q = 0; q < K; ++q) {
             const u32 j = lt + q * G;
-            if (q < nq && j < I.n)
-                od[out_pos(perm, I.st + j)] = (LIN[q] != NOPIX) ? int32_t(u32(gp.acc[AR[q] >> 16])) : -1;
+            if (q < nq && j < I.n) {
+                int32_t id = -1;
+                if (has(valid, q)) {
+                    const u64 v = gp.acc[X[q]];
+                    const u32 charge = u32(v), row = RC[q] & 0xFFFFu, c = RC[q] >> 16;
+                    const bool keep = charge >= a.charge_cut;
+                    if (keep) id = int32_t(idbase + u32(v >> 47));
+                    if (keep && (hits || has(starts, q))) {
+                        const u32 p = I.st + position(X[q]);
+                        if (has(starts, q)) {
+                            tid_[p] = id;
+                            tch[p] = int32_t(charge);
+                            tsz[p] = int32_t(u32(v >> 32) & 0x7FFFu);
+                        }
+                        if (hits) {
+                            const u64 w = A[q] & 0xFFFFu;
+                            atomicAdd(&hs[2 * p], w * c);
+                            atomicAdd(&hs[2 * p + 1], w * row);
+                        }
+                    }
+                    st_wg(&gp.bm[BM_FRONT + c * WPC + (row >> 5)], 0u);   // several digis may share a word
+                }
+                od[out_pos(perm, I.st + j)] = id;
+            }
         }
-#pragma unroll
-        for (u32 q = 0; q < K; ++q)
-            if (q < nq && LIN[q] != NOPIX) st_wg(&gp.bm[LIN[q] >> 5], 0u);   // several digis may share a word
         if (lt < CMW) gp.cm[lt] = 0u;
         if (err) atomicOr(ws_ptr<u32>(E, L.ctl) + CTL_ERR, err);
     }
@@ -1244,7 +1166,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     const u32 tid = threadIdx.x, g = tid / G, lt = tid % G;
     const u32 gofs = WAVE ? 0u : g;
     RegModuleSmem<G, K>& gp = s.grp[g];
-    for (u32 w = lt; w < WORDS; w += G) gp.bm[w] = 0u;
+    for (u32 w = lt; w < BM_WORDS; w += G) gp.bm[w] = 0u;
     if (lt < CMW) gp.cm[lt] = 0u;
     const u32 k = num_events(a);
     // Without the segmentation kernel (one event): every module is a unit, its
@@ -1398,12 +1320,11 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
         if (base + gofs < total && !I.ok && lt == 0) skip(E, I);
         if (!WAVE || I.ok) {
             const EvLayout L = ev_layout(E.cap, a.n_modules);
-            cluster_regs<G, K>(a, E, L, I, gp, lt, RC, A, mid);
+            cluster_regs<G, K, MPW == 1>(a, E, L, I, gp, lt, RC, A, mid);
         } else {
             mid(0);
             mid(1);
             mid(2);
-            mid(3);
         }
         base = nbase;
         E = En;
@@ -1418,55 +1339,229 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
 // ---------------------------------------------------------------------------
 // big: one module per 512-thread workgroup
 // ---------------------------------------------------------------------------
-// Scratch mode (more than BIG_RCAP digis).  Connectivity is computed on the bitmap
-// alone: every vertical run is linked to the runs of the next column that touch it,
-// with the parents of up to MAX_RUNS runs in LDS.  The roots, in run order (= order
-// of their smallest linear index), number the clusters.  Three passes over the digis
-// follow: charge and size (device atomics into the module's slice of the event's
-// final charge/size arrays, which the compaction kernel overwrites later; a wave
-// whose digis all belong to one cluster adds once), then per-digi ids.
-template <u32 BW>
-struct BigScratchSmem {
-    u32 bm[WORDS];
-    u32 par[MAX_RUNS];
-    u32 rootb[MAX_RUNS / 32];   // root runs, then kept clusters (over cluster index)
-    u16 rpre[WORDS];
-    u16 rootp[MAX_RUNS / 32];   // roots before each word, then kept clusters before each word
-    u32 wsum[BW / 64];
-    u32 misc[4];
+// Register mode: up to BIG_RCAP digis, K per thread of a 1,024-thread workgroup.  At such
+// occupancies most work is per digi, and one workgroup has the compute unit to itself (the
+// words of up to BIG_RCAP runs take 128 KB), so what bounds it is the instructions its
+// sixteen waves issue: run parents and links come from the bitmap, a word of 32 rows at a
+// time, trees are flattened per run, and a digi looks its run up in one column entry and
+// one bitmap word and adds to its root.  186 modules of 13,312 digis: 58 -> 34 us (512
+// threads of 32 digis, links listed and united one by one, before).
+template <u32 G, u32 K>
+struct DenseSmem {
+    static constexpr u32 RCAP = G * K, KBW = RCAP / 32;
+    u32 bm[BM_WORDS];  // fired-pixel bitmap (clear between modules)
+    u64 col[COLS + 2]; // entry c+1: column c's run numbers
+    u64 acc[RCAP];     // per run, as RegModuleSmem::acc
+    u32 kb[KBW];       // kept-root bits over run index
+    u16 kpre[KBW];     // kept roots before each kb word
+    u32 wsum[G / 64];
 };
 
-constexpr u32 UNR = 8;                        // digis per thread fetched at once
-
-__device__ __forceinline__ u32 clampj(u32 j, u32 n) { return j < n ? j : 0u; }
-
-// Add `val` at base[key] for every lane with `valid`; one atomic per wave when all
-// valid lanes share the key.  Called by all lanes of the wave.
-__device__ __forceinline__ void wave_add(u32* base, u32 key, u32 val, bool valid) {
-    const u64 vm = __ballot(valid);
-    if (!vm) return;
-    const u32 first = __ffsll((unsigned long long)vm) - 1;
-    const u32 lead = __shfl(key, first, 64);
-    const u64 same = __ballot(valid && key == lead);
-    if (same == vm) {
-        u32 sum = valid ? val : 0u;
+template <u32 G, u32 K>
+__device__ __forceinline__ void cluster_dense(const LaunchArgs& a, const EventDesc& E, const EvLayout& L, const Item& I,
+                                              DenseSmem<G, K>& s) {
+    constexpr u32 KBW = G * K / 32;
+    static_assert(G >= COLS && KBW <= G, "a thread per column, and per word of kept bits");
+    static_assert(G * K <= 16384, "sizes of up to 15 bits, run numbers of up to 16");
+    const u32 tid = threadIdx.x, n = I.n, st = I.st;
+    const u32 nq = min((n + G - 1) / G, K);
+    const u16 *prow = (const u16*)E.row + st, *pcol = (const u16*)E.col + st, *padc = (const u16*)E.adc + st;
+    const bool hits = (E.flags & EF_HITS) != 0;
+    u32 RC[K], A[K], X[K], valid = 0, err = 0, dup = 0;
 #pragma unroll
-        for (u32 d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-        if ((threadIdx.x & 63u) == first) atomicAdd(&base[lead], sum);
-    } else if (valid) {
-        atomicAdd(&base[key], val);
+    for (u32 q = 0; q < K; ++q) {                              // every slot loads a digi of the module
+        const u32 j = tid + q * G < n ? tid + q * G : 0u;
+        RC[q] = u32(prow[j]) | (u32(pcol[j]) << 16);
+        A[q] = padc[j];
+    }
+    if (tid < KBW) s.kb[tid] = 0u;
+#pragma unroll
+    for (u32 q = 0; q < K; ++q)
+        if (q < nq && tid + q * G < n) {
+            const u32 row = RC[q] & 0xFFFFu, c = RC[q] >> 16, bit = 1u << (row & 31u);
+            if (row < ROWS && c < COLS) {
+                dup |= atomicOr(&s.bm[BM_FRONT + c * WPC + (row >> 5)], bit) & bit;
+                valid |= 1u << q;
+            } else {
+                err |= EB_RANGE;
+            }
+        }
+    if (dup) err |= EB_DUP;
+    lds_barrier();
+    u32 nruns;
+    {
+        u32 cnt = 0;
+        u64 e = 0ull;
+        if (tid < COLS) e = col_entry(s.bm, tid, cnt);
+        const u32 run = group_excl_scan<G>(cnt, tid, s.wsum, nruns);
+        if (tid < COLS) s.col[tid + 1] = e | run;
+    }
+    lds_barrier();
+    for (u32 u = tid; u < WORDS; u += G)                       // first parents (rule B), sums zero
+        word_parents(s.bm, s.col, u / WPC, u % WPC, [&](u32 run, u32 parent) { s.acc[run] = u64(parent) << 48; });
+    lds_barrier();
+    for (u32 u = tid; u < WORDS; u += G)                       // rule A
+        word_links(s.bm, s.col, u / WPC, u % WPC, [&](u32 x, u32 y) { unite_packed(s.acc, x, y); });
+    lds_barrier();
+    // every run points at its root: a thread moves only its own runs' parents, each to an
+    // ancestor, so what it stores last (the root) stands; others' moves double the steps
+    for (u32 base = 0; base < nruns; base += 4 * G) {
+        u32 x[4], more, it = 0;
+#pragma unroll
+        for (u32 u = 0; u < 4; ++u) x[u] = min(base + u * G + tid, nruns - 1);
+        do {
+            u32 p[4];
+            more = 0;
+#pragma unroll
+            for (u32 u = 0; u < 4; ++u) p[u] = parent_of(s.acc, x[u]);
+#pragma unroll
+            for (u32 u = 0; u < 4; ++u) {
+                more |= p[u] ^ x[u];
+                x[u] = p[u];
+                if (base + u * G + tid < nruns) st_wg(hi_word(s.acc, base + u * G + tid), p[u] << 16);
+            }
+        } while (more && ++it < MAX_RUNS);
+    }
+    lds_barrier();
+#pragma unroll
+    for (u32 q = 0; q < K; ++q)                                // roots, charge and size
+        if (q < nq && ((valid >> q) & 1u)) {
+            const u32 row = RC[q] & 0xFFFFu, c = RC[q] >> 16, k = row >> 5;
+            X[q] = parent_of(s.acc, run_number(s.col[c + 1], k, s.bm[BM_FRONT + c * WPC + k], row));
+        }
+#pragma unroll
+    for (u32 q = 0; q < K; ++q)
+        if (q < nq && ((valid >> q) & 1u)) atomicAdd(&s.acc[X[q]], (1ull << 32) | u64(A[q]));
+    lds_barrier();
+    for (u32 u = tid; u < WORDS; u += G) {                     // cut; first pixel and size of the roots
+        const ColWord x = col_word(s.bm, s.col, u / WPC, u % WPC);
+        u32 m = x.st, r = x.r0;
+        while (m) {
+            const u32 b = __builtin_ctz(m);
+            m &= m - 1u;
+            const u64 v = s.acc[r];
+            if (u32(v >> 48) == r) {
+                if (u32(v) >= a.charge_cut) atomicOr(&s.kb[r >> 5], 1u << (r & 31u));
+                st_wg(hi_word(s.acc, r), (((u << 5) + b) << 15) | (u32(v >> 32) & 0x7FFFu));
+            }
+            ++r;
+        }
+    }
+    lds_barrier();
+    u32 Kc;
+    {
+        const u32 cnt = tid < KBW ? __popc(s.kb[tid]) : 0u;
+        const u32 pre = group_excl_scan<G>(cnt, tid, s.wsum, Kc);
+        if (tid < KBW) s.kpre[tid] = u16(pre);
+    }
+    lds_barrier();
+    if (tid == 0) ws_ptr<u32>(E, L.kept)[I.it] = Kc;
+    const u32 idbase = I.mod * PIX;
+    // f(root, position) for the kept clusters
+    auto kept_roots = [&](auto f) {
+        for (u32 r = tid; r < nruns; r += G) {
+            const u32 w = s.kb[r >> 5], bit = 1u << (r & 31u);
+            if (w & bit) f(r, st + u32(s.kpre[r >> 5]) + __popc(w & (bit - 1u)));
+        }
+    };
+    {
+        int32_t* tid_ = ws_ptr<int32_t>(E, L.tid);
+        int32_t* tch = ws_ptr<int32_t>(E, L.tcharge);
+        int32_t* tsz = ws_ptr<int32_t>(E, L.tsize);
+        kept_roots([&](u32 r, u32 p) {
+            const u64 v = s.acc[r];
+            tid_[p] = int32_t(idbase + u32(v >> 47));
+            tch[p] = int32_t(u32(v));
+            tsz[p] = int32_t(u32(v >> 32) & 0x7FFFu);
+        });
+    }
+    int32_t* od = (int32_t*)E.o_digi;
+    const u32* perm = perm_of(E, L);
+    u32 keep = 0;
+#pragma unroll
+    for (u32 q = 0; q < K; ++q) {
+        const u32 j = tid + q * G;
+        if (q < nq && j < n) {
+            int32_t id = -1;
+            if ((valid >> q) & 1u) {
+                const u64 v = s.acc[X[q]];
+                if (u32(v) >= a.charge_cut) {
+                    id = int32_t(idbase + u32(v >> 47));
+                    keep |= 1u << q;
+                }
+            }
+            od[out_pos(perm, st + j)] = id;
+        }
+    }
+    for (u32 w = tid; w < WORDS; w += G) s.bm[BM_FRONT + w] = 0u;
+    if (err) atomicOr(ws_ptr<u32>(E, L.ctl) + CTL_ERR, err);
+    lds_barrier();
+    if (hits) {                                                // exact sums in LDS, columns, then rows
+        u64* hs = ws_ptr<u64>(E, L.hsum);
+        for (u32 axis = 0; axis < 2; ++axis) {
+            kept_roots([&](u32 r, u32) { s.acc[r] = 0ull; });
+            lds_barrier();
+#pragma unroll
+            for (u32 q = 0; q < K; ++q)
+                if (q < nq && ((keep >> q) & 1u))
+                    atomicAdd(&s.acc[X[q]], u64(A[q]) * (axis ? RC[q] & 0xFFFFu : RC[q] >> 16));
+            lds_barrier();
+            kept_roots([&](u32 r, u32 p) { hs[2 * p + axis] = s.acc[r]; });
+            lds_barrier();
+        }
     }
 }
 
-// The same for 64-bit sums in LDS.
-__device__ __forceinline__ void wave_add_lds64(u64* base, u32 key, u64 val, bool valid) {
+// Scratch mode (more than BIG_RCAP digis).  Connectivity is computed on the bitmap
+// alone, with the parents of up to MAX_RUNS runs in LDS: every run starts under its rule B
+// run (a chain along the columns, at most COLS long), pointer doubling flattens the chains,
+// and only rule A's links need unions.  The roots, in run order (= order of their smallest
+// linear index), number the clusters.  Three passes over the digis: bitmap; charge and
+// size (LDS sums of the first LCAP clusters, device atomics into the module's slice of the
+// event's final charge/size arrays, which the compaction kernel overwrites later, for the
+// rest), leaving each digi's cluster in its output word; per-digi ids from that.  The passes
+// take four digis per load and test the ranges of four at once.  Like register mode it is
+// bound by the instructions of one workgroup: a serpentine 159 -> 84 us (before: unions
+// column by column, a lane per row, 60-85 us of it; one digi per load; runs looked up again
+// for the ids).
+template <u32 BW>
+struct BigScratchSmem {
+    u32 bm[BM_WORDS];
+    alignas(8) u32 par[MAX_RUNS];   // its second half later holds 64-bit sums
+    u32 rootb[MAX_RUNS / 32];   // root runs, then kept clusters (over cluster index)
+    u64 col[COLS + 2];          // entry c+1: column c's run numbers
+    u16 rootp[MAX_RUNS / 32];   // roots before each word, then kept clusters before each word
+    u32 wsum[BW / 64];
+};
+
+constexpr u32 UNR = 4;                        // groups of 4 digis per thread fetched at once
+
+// Four consecutive 16-bit values at any 2-byte address as one 8-byte load, four 32-bit
+// ones at any 4-byte address as one 16-byte access (global memory takes both unaligned).
+struct __attribute__((packed, aligned(2))) U16x4 {
+    u64 v;
+};
+struct __attribute__((packed, aligned(4))) I32x4 {
+    int32_t v[4];
+};
+__device__ __forceinline__ u64 load4(const u16* p) { return reinterpret_cast<const U16x4*>(p)->v; }
+__device__ __forceinline__ u32 part(u64 v, u32 i) { return u32(v >> (16 * i)) & 0xFFFFu; }
+// Some of the four values is `limit` (at most 2^15) or more.
+__device__ __forceinline__ bool any_at_least(u64 v, u32 limit) {
+    return ((v | (v + u64(0x8000u - limit) * 0x0001000100010001ull)) & 0x8000800080008000ull) != 0ull;
+}
+
+// Add `val` to base[key] for every lane with `valid`; one atomic per wave when all
+// valid lanes share the key.  Called by all lanes of the wave.
+template <typename T>
+__device__ __forceinline__ void wave_add(T* base, u32 key, T val, bool valid) {
     const u64 vm = __ballot(valid);
     if (!vm) return;
     const u32 first = __ffsll((unsigned long long)vm) - 1;
     const u32 lead = __shfl(key, first, 64);
     const u64 same = __ballot(valid && key == lead);
     if (same == vm) {
-        u64 sum = valid ? val : 0ull;
+        T sum = valid ? val : T(0);
 #pragma unroll
         for (u32 d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
         if ((threadIdx.x & 63u) == first) atomicAdd(&base[lead], sum);
@@ -1478,9 +1573,9 @@ __device__ __forceinline__ void wave_add_lds64(u64* base, u32 key, u64 val, bool
 template <u32 BW>
 __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const EventDesc& E, const EvLayout& L,
                                                 const Item& I, BigScratchSmem<BW>& s) {
-    constexpr u32 WPT = (WORDS + BW - 1) / BW;
     constexpr u32 KW = MAX_RUNS / 32, KPT = (KW + BW - 1) / BW;
-    constexpr u32 SPAN = UNR * BW;
+    constexpr u32 SPAN = 4 * UNR * BW;                     // digis per step
+    static_assert(BW >= COLS, "a thread per column");
     const u32 tid = threadIdx.x, n = I.n, st = I.st;
     u32* cid = (u32*)E.o_id + st;       // per cluster: id (or -1 once cut)
     u32* cch = (u32*)E.o_charge + st;   // per cluster: charge
@@ -1490,105 +1585,108 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     const bool hits = (E.flags & EF_HITS) != 0;
     u64* hs = ws_ptr<u64>(E, L.hsum);
     u32 err = 0;
-    // UNR digis' linear index (NOPIX when absent or out of range), loads first
-    auto fetch = [&](u32 base, u32* lin, u32* adc) {
-        u32 r[UNR], c[UNR];
-#pragma unroll
-        for (u32 u = 0; u < UNR; ++u) {
-            const u32 i = st + clampj(base + u * BW + tid, n);
-            r[u] = E.row[i];
-            c[u] = E.col[i];
-            if (adc) adc[u] = E.adc[i];
-        }
-#pragma unroll
-        for (u32 u = 0; u < UNR; ++u) {
-            const u32 j = base + u * BW + tid;
-            lin[u] = (j < n && r[u] < ROWS && c[u] < COLS) ? c[u] * ROWS + r[u] : NOPIX;
-            if (j < n && lin[u] == NOPIX) err |= EB_RANGE;
-        }
-    };
+    const u16 *prow = (const u16*)E.row + st, *pcol = (const u16*)E.col + st, *padc = (const u16*)E.adc + st;
     const u32 wv = tid >> 6, lane = tid & 63u;
-    // cluster index of run `run` (after the flattening below, par[run] is its root)
-    auto cluster_of = [&](u32 run) {
+    // A step: this thread's digis base + 4 * (u * BW + tid) + 0..3, u < UNR; quads past the
+    // module's end are passed over by the whole workgroup.
+    auto first_of = [&](u32 base, u32 u) { return base + 4u * (u * BW + tid); };
+    auto some = [&](u32 base, u32 u) { return base + 4u * u * BW < n; };
+    auto quad = [&](const u16* p, u32 base, u32 u) -> u64 {
+        const u32 first = first_of(base, u);
+        if (base + 4u * (u + 1) * BW <= n) return load4(p + first);
+        u64 v = 0ull;
+        for (u32 i = 0; i < 4; ++i)
+            if (first + i < n) v |= u64(p[first + i]) << (16 * i);
+        return v;
+    };
+    // the wave's quads hold four pixels each (else each digi is looked at by itself)
+    auto whole = [&](u32 base, u32 u, u64 r, u64 c) {
+        return __ballot(first_of(base, u) + 4 > n || any_at_least(r, ROWS) || any_at_least(c, COLS)) == 0ull;
+    };
+    auto pixel = [&](u32 j, u32 row, u32 col) { return j < n && row < ROWS && col < COLS; };
+    auto word_of = [&](u32 row, u32 col) { return BM_FRONT + col * WPC + (row >> 5); };
+    auto cluster_of = [&](u32 run) {                      // of a flattened run (par[run] is its root)
         const u32 root = ld_wg(&s.par[run]);
         return u32(s.rootp[root >> 5]) + __popc(s.rootb[root >> 5] & ((1u << (root & 31u)) - 1u));
     };
-    // s.rootb[] over all KW words: bit r set iff pred(r); a wave forms 64 bits at a time
-    // from 64 consecutive indices (ballot), so lanes touch consecutive words
-    auto set_bits = [&](auto pred) {
-        for (u32 base = wv * 64; base < KW * 32; base += BW) {
-            const u64 m = __ballot(pred(base + lane) ? 1 : 0);
-            if (lane == 0) {
-                s.rootb[base >> 5] = u32(m);
-                s.rootb[(base >> 5) + 1] = u32(m >> 32);
-            }
-        }
-    };
     for (u32 base = 0; base < n; base += SPAN) {               // pass 1: bitmap
-        u32 lin[UNR];
-        fetch(base, lin, nullptr);
+        u64 r[UNR], c[UNR];
 #pragma unroll
         for (u32 u = 0; u < UNR; ++u)
-            if (lin[u] != NOPIX) {
-                const u32 bit = 1u << (lin[u] & 31u);
-                if (atomicOr(&s.bm[lin[u] >> 5], bit) & bit) err |= EB_DUP;
+            if (some(base, u)) {
+                r[u] = quad(prow, base, u);
+                c[u] = quad(pcol, base, u);
             }
+        u32 dup = 0;
+#pragma unroll
+        for (u32 u = 0; u < UNR; ++u) {
+            if (!some(base, u)) continue;
+            const bool all = whole(base, u, r[u], c[u]);
+#pragma unroll
+            for (u32 i = 0; i < 4; ++i) {
+                const u32 row = part(r[u], i), col = part(c[u], i), bit = 1u << (row & 31u);
+                if (all || pixel(first_of(base, u) + i, row, col)) dup |= atomicOr(&s.bm[word_of(row, col)], bit) & bit;
+                else if (first_of(base, u) + i < n) err |= EB_RANGE;
+            }
+        }
+        if (dup) err |= EB_DUP;
     }
     lds_barrier();
     u32 nruns;
     {                                                           // runs
-        u32 sw[WPT], cnt = 0;
+        u32 cnt = 0;
+        u64 e = 0ull;
+        if (tid < COLS) e = col_entry(s.bm, tid, cnt);
+        const u32 run = group_excl_scan<BW>(cnt, tid, s.wsum, nruns);
+        if (tid < COLS) s.col[tid + 1] = e | run;
+    }
+    lds_barrier();
+    for (u32 u = tid; u < WORDS; u += BW)                       // first parents
+        word_parents(s.bm, s.col, u / WPC, u % WPC, [&](u32 run, u32 parent) { st_wg(&s.par[run], parent); });
+    lds_barrier();
+    // Every run points at its root.  A thread moves only its own runs' parents, each to an
+    // ancestor, so what it stores last (the root) stands; others' moves double the steps.
+    // `last`: one bit per root too.
+    auto flatten = [&](bool last) {
+        constexpr u32 F = 4;
+        for (u32 base = 0; base < nruns; base += F * BW) {
+            u32 x[F], more;
 #pragma unroll
-        for (u32 i = 0; i < WPT; ++i) {
-            const u32 w = tid * WPT + i;
-            sw[i] = w < WORDS ? __popc(run_starts(s.bm, w)) : 0u;
-            cnt += sw[i];
-        }
-        u32 run = group_excl_scan<BW>(cnt, tid, s.wsum, nruns);
+            for (u32 u = 0; u < F; ++u) x[u] = min(base + u * BW + tid, nruns - 1);
+            u32 it = 0;
+            do {
+                u32 p[F];
+                more = 0;
 #pragma unroll
-        for (u32 i = 0; i < WPT; ++i) {
-            const u32 w = tid * WPT + i;
-            if (w < WORDS) s.rpre[w] = u16(run);
-            run += sw[i];
+                for (u32 u = 0; u < F; ++u) p[u] = ld_wg(&s.par[x[u]]);
+#pragma unroll
+                for (u32 u = 0; u < F; ++u) {
+                    more |= p[u] ^ x[u];
+                    x[u] = p[u];
+                    if (base + u * BW + tid < nruns) st_wg(&s.par[base + u * BW + tid], p[u]);
+                }
+            } while (more && ++it < MAX_RUNS);
+            if (last) {
+#pragma unroll
+                for (u32 u = 0; u < F; ++u) {
+                    const u32 r = base + u * BW + tid;
+                    const u64 m = __ballot(r < nruns && x[u] == r ? 1 : 0);
+                    if (lane == 0 && r < nruns) {
+                        s.rootb[r >> 5] = u32(m);
+                        s.rootb[(r >> 5) + 1] = u32(m >> 32);
+                    }
+                }
+            }
         }
-    }
-    for (u32 r = tid; r < nruns; r += BW) s.par[r] = r;
+        lds_barrier();
+    };
+    for (u32 w = tid; w < KW; w += BW) s.rootb[w] = 0u;
+    flatten(false);
+    for (u32 u = tid; u < WORDS; u += BW)                       // rule A
+        word_links(s.bm, s.col, u / WPC, u % WPC, [&](u32 x, u32 y) { uf_unite(s.par, x, y); });
     lds_barrier();
-    // Unions from the bitmap only.  Wave v links the runs of its block of columns to the
-    // next column, one column at a time from left to right, a lane per row.
-    // A run of the next column is then hooked straight under a root found in an earlier
-    // column, so the trees stay shallow even along chains that cross the module (a
-    // serpentine); unordered unions would build paths as long as the chain.
-    {
-        constexpr u32 NWV = BW / 64;
-        const u32 c0 = wv * COLS / NWV, c1 = (wv + 1) * COLS / NWV;
-        ColPair cur;
-        if (c0 < c1 && c0 + 1 < COLS) load_pair(cur, s.bm, s.rpre, c0);
-        for (u32 col = c0; col < c1 && col + 1 < COLS; ++col) {
-            ColPair nxt;
-            const bool more = col + 1 < c1 && col + 2 < COLS;
-            if (more) load_pair(nxt, s.bm, s.rpre, col + 1);   // the bitmap is read-only here
-            link_pair(s.par, cur, lane);
-            gsync<64>();                                        // this column's hooks before the next
-            if (more) cur = nxt;
-        }
-    }
-    lds_barrier();
-    // flatten: every run points at its root.  Walks only read, and each store writes a
-    // root, so a concurrent walk through a stored entry still ends at the same root.
-    for (u32 r = tid; r < nruns; r += BW) {
-        u32 x = ld_wg(&s.par[r]);
-        for (u32 it = 0; it < MAX_RUNS; ++it) {
-            const u32 y = ld_wg(&s.par[x]);
-            if (y == x) break;
-            x = y;
-        }
-        st_wg(&s.par[r], x);
-    }
-    lds_barrier();
-    // roots (parent == self) number the clusters in order of their smallest index
-    set_bits([&](u32 r) { return r < nruns && ld_wg(&s.par[r]) == r; });
-    lds_barrier();
+    // the roots number the clusters in order of their smallest index
+    flatten(true);
     u32 ncl;
     {
         u32 sw[KPT], cnt = 0;
@@ -1612,6 +1710,7 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     // first LCAP clusters' charge | size << 44 (LDS atomics), the others' sums go to
     // device memory.
     constexpr u32 RPT = (MAX_RUNS + BW - 1) / BW, LCAP = MAX_RUNS * 2 / 8;
+    static_assert((offsetof(BigScratchSmem<BW>, par) + size_t(MAX_RUNS) * 2) % 8 == 0, "64-bit LDS atomics need 8-byte alignment");
     u16* cl = reinterpret_cast<u16*>(s.par);
     u64* acc = reinterpret_cast<u64*>(reinterpret_cast<u8*>(s.par) + size_t(MAX_RUNS) * 2);
     {
@@ -1633,15 +1732,15 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     lds_barrier();
     // per cluster: id from the start of its root run; zero the sums
     for (u32 c = tid; c < min(ncl, LCAP); c += BW) acc[c] = 0ull;
-    for (u32 w = tid; w < WORDS; w += BW) {
-        u32 sb = run_starts(s.bm, w);
-        u32 r = s.rpre[w];
-        while (sb) {
-            const u32 b = __ffs(sb) - 1;
-            sb &= sb - 1;
+    for (u32 u = tid; u < WORDS; u += BW) {
+        const ColWord x = col_word(s.bm, s.col, u / WPC, u % WPC);
+        u32 m = x.st, r = x.r0;
+        while (m) {
+            const u32 b = __builtin_ctz(m);
+            m &= m - 1u;
             if (s.rootb[r >> 5] & (1u << (r & 31u))) {
                 const u32 c = u32(s.rootp[r >> 5]) + __popc(s.rootb[r >> 5] & ((1u << (r & 31u)) - 1u));
-                cid[c] = I.mod * PIX + (w << 5) + b;
+                cid[c] = I.mod * PIX + (u << 5) + b;
                 if (c >= LCAP) {
                     cch[c] = 0u;
                     csz[c] = 0u;
@@ -1652,44 +1751,80 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     }
     wait_all_mem();
     lds_barrier();
+    // Digi outputs at their own positions, and every cluster's sums in LDS: the usual case,
+    // taken by the whole workgroup.
+    const bool plain = !perm && ncl <= LCAP;
+    auto cluster_at = [&](u32 row, u32 col) {
+        return u32(cl[run_number(s.col[col + 1], row >> 5, s.bm[word_of(row, col)], row)]);
+    };
+    // A thread whose four digis belong to one cluster adds them to a running sum, which it
+    // hands on when the cluster changes; of the last ones a wave whose threads all hold the
+    // same cluster (a serpentine) makes one atomic.
+    u32 run_c = 0;
+    u64 run_sum = 0;
     for (u32 base = 0; base < n; base += SPAN) {               // pass 2: charge and size
-        u32 lin[UNR], adc[UNR];
-        fetch(base, lin, adc);
-        u32 c[UNR];
-#pragma unroll
-        for (u32 u = 0; u < UNR; ++u) c[u] = lin[u] != NOPIX ? u32(cl[run_of(s.bm, s.rpre, lin[u])]) : 0u;
-        // when each thread's digis here belong to one cluster (a cluster spanning the
-        // module, as in a serpentine), the thread adds them up first: one wave sum
-        // instead of one per slot
-        u32 c0 = NOPIX;
-        u64 tot = 0;
-        bool one = true;
+        u64 r[UNR], c[UNR], w[UNR];
 #pragma unroll
         for (u32 u = 0; u < UNR; ++u)
-            if (lin[u] != NOPIX) {
-                one = one && (c0 == NOPIX || c[u] == c0);
-                c0 = c[u];
-                tot += (1ull << 44) | adc[u];
+            if (some(base, u)) {
+                r[u] = quad(prow, base, u);
+                c[u] = quad(pcol, base, u);
+                w[u] = quad(padc, base, u);
             }
-        if (__ballot(!one) == 0ull) {
-            const bool v = c0 != NOPIX;
-            wave_add_lds64(acc, c0, tot, v && c0 < LCAP);
-            wave_add(cch, c0, u32(tot & 0xFFFFFFFFFFFull), v && c0 >= LCAP);
-            wave_add(csz, c0, u32(tot >> 44), v && c0 >= LCAP);
-        } else {
 #pragma unroll
-            for (u32 u = 0; u < UNR; ++u) {
-                const bool v = lin[u] != NOPIX;
-                wave_add_lds64(acc, c[u], (1ull << 44) | adc[u], v && c[u] < LCAP);
-                wave_add(cch, c[u], adc[u], v && c[u] >= LCAP);
-                wave_add(csz, c[u], 1u, v && c[u] >= LCAP);
+        for (u32 u = 0; u < UNR; ++u) {
+            if (!some(base, u)) continue;
+            const u32 j = first_of(base, u);
+            if (plain && whole(base, u, r[u], c[u])) {
+                I32x4 cc;
+                u32 sum = 0;
+                bool one = true;
+#pragma unroll
+                for (u32 i = 0; i < 4; ++i) {
+                    cc.v[i] = int32_t(cluster_at(part(r[u], i), part(c[u], i)));
+                    one = one && cc.v[i] == cc.v[0];
+                    sum += part(w[u], i);
+                }
+                *reinterpret_cast<I32x4*>(od + st + j) = cc;    // for pass 3
+                if (one) {
+                    if (u32(cc.v[0]) != run_c) {
+                        if (run_sum) atomicAdd(&acc[run_c], run_sum);
+                        run_c = u32(cc.v[0]);
+                        run_sum = 0;
+                    }
+                    run_sum += (4ull << 44) | sum;
+                } else {
+#pragma unroll
+                    for (u32 i = 0; i < 4; ++i) atomicAdd(&acc[cc.v[i]], (1ull << 44) | u64(part(w[u], i)));
+                }
+                continue;
+            }
+#pragma unroll 1
+            for (u32 i = 0; i < 4; ++i) {
+                const u32 row = part(r[u], i), col = part(c[u], i), x = part(w[u], i);
+                const bool v = pixel(j + i, row, col);
+                const u32 k = v ? cluster_at(row, col) : 0u;
+                if (j + i < n) od[out_pos(perm, st + j + i)] = v ? int32_t(k) : -1;
+                wave_add<u64>(acc, k, (1ull << 44) | u64(x), v && k < LCAP);
+                wave_add<u32>(cch, k, x, v && k >= LCAP);
+                wave_add<u32>(csz, k, 1u, v && k >= LCAP);
             }
         }
     }
+    wave_add<u64>(acc, run_c, run_sum, run_sum != 0);
     wait_all_mem();
     lds_barrier();
-    // cut; kept clusters -> staging records in cluster (= ascending id) order
-    set_bits([&](u32 c) { return c < ncl && (c < LCAP ? u32(acc[c]) : ld_ag(&cch[c])) >= a.charge_cut; });
+    // cut, one bit per kept cluster (64 at a time by ballot, so that lanes touch
+    // consecutive words); kept clusters -> staging records in cluster (= ascending id) order
+    for (u32 base = wv * 64; base < KW * 32; base += BW) {
+        const u32 c = base + lane;
+        u64 m = 0ull;
+        if (base < ncl) m = __ballot(c < ncl && (c < LCAP ? u32(acc[c]) : ld_ag(&cch[c])) >= a.charge_cut ? 1 : 0);
+        if (lane == 0) {
+            s.rootb[base >> 5] = u32(m);
+            s.rootb[(base >> 5) + 1] = u32(m >> 32);
+        }
+    }
     lds_barrier();
     u32 Kc;
     {
@@ -1728,9 +1863,8 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
                     tsz[st + pos] = int32_t(lds ? u32(v >> 44) : ld_ag(&csz[c]));
                     ++pos;
                     if (lds) acc[c] = u64(id);                  // for the per-digi ids
-                } else if (lds) {
-                    acc[c] = u64(NOPIX);
                 } else {
+                    if (lds) acc[c] = u64(NOPIX);
                     st_ag(&cid[c], NOPIX);
                 }
             }
@@ -1739,28 +1873,56 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     }
     wait_all_mem();
     lds_barrier();
+    if (hits) {
+        // Weighted coordinates of the kept clusters: columns, then rows, in the LDS sums (the
+        // records' device sums take them whole), those of clusters beyond them by device
+        // atomics.  One device atomic per digi took 1.25 ms for a 33,423-pixel serpentine.
+        for (u32 axis = 0; axis < 2; ++axis) {
+            const u16* pc = axis ? prow : pcol;
+            for (u32 c = tid; c < min(ncl, LCAP); c += BW) acc[c] = 0ull;
+            lds_barrier();
+            for (u32 j0 = 0; j0 < n; j0 += BW) {
+                const u32 j = j0 + tid;
+                const int32_t k = j < n ? od[out_pos(perm, st + j)] : -1;
+                const u64 x = k >= 0 ? u64(padc[j]) * pc[j] : 0ull;
+                const u32 c = k >= 0 ? u32(k) : 0u;
+                const bool kept = k >= 0 && ((s.rootb[c >> 5] >> (c & 31u)) & 1u);
+                wave_add<u64>(acc, c, x, kept && c < LCAP);
+                if (kept && c >= LCAP) atomicAdd(&hs[2 * (st + s.rootp[c >> 5] + __popc(s.rootb[c >> 5] & ((1u << (c & 31u)) - 1u))) + axis], x);
+            }
+            lds_barrier();
+            for (u32 c = tid; c < min(ncl, LCAP); c += BW)
+                if ((s.rootb[c >> 5] >> (c & 31u)) & 1u)
+                    hs[2 * (st + s.rootp[c >> 5] + __popc(s.rootb[c >> 5] & ((1u << (c & 31u)) - 1u))) + axis] = acc[c];
+            lds_barrier();
+        }
+        for (u32 c = tid; c < min(ncl, LCAP); c += BW) acc[c] = u64(ld_ag(&cid[c]));
+        lds_barrier();
+    }
     for (u32 base = 0; base < n; base += SPAN) {               // pass 3: per-digi ids
-        u32 lin[UNR], adc3[UNR];
-        fetch(base, lin, hits ? adc3 : nullptr);
-        u32 c[UNR];
 #pragma unroll
-        for (u32 u = 0; u < UNR; ++u) c[u] = lin[u] != NOPIX ? u32(cl[run_of(s.bm, s.rpre, lin[u])]) : 0u;
+        for (u32 u = 0; u < UNR; ++u) {                         // over what this thread left in pass 2
+            if (!some(base, u)) continue;
+            const u32 j = first_of(base, u);
+            if (plain && __ballot(j + 4 > n) == 0ull) {
+                I32x4 cc = *reinterpret_cast<const I32x4*>(od + st + j);
 #pragma unroll
-        for (u32 u = 0; u < UNR; ++u) {
-            const u32 j = base + u * BW + tid;
-            const u32 id = c[u] < LCAP ? u32(acc[c[u]]) : ld_ag(&cid[c[u]]);
-            if (j < n) od[out_pos(perm, st + j)] = lin[u] != NOPIX ? int32_t(id) : -1;
-            if (hits && lin[u] != NOPIX && id != NOPIX) {           // kept: add to its record's sums
-                const u32 cw = c[u] >> 5, q = st + s.rootp[cw] + __popc(s.rootb[cw] & ((1u << (c[u] & 31u)) - 1u));
-                const u64 w = adc3[u], col = lin[u] / ROWS;
-                atomicAdd(&hs[2 * q], w * col);
-                atomicAdd(&hs[2 * q + 1], w * (lin[u] - col * ROWS));
+                for (u32 i = 0; i < 4; ++i) cc.v[i] = cc.v[i] >= 0 ? int32_t(u32(acc[cc.v[i]])) : -1;
+                *reinterpret_cast<I32x4*>(od + st + j) = cc;
+                continue;
+            }
+#pragma unroll 1
+            for (u32 i = 0; i < 4; ++i) {
+                if (j + i >= n) continue;
+                const u32 q = out_pos(perm, st + j + i);
+                const int32_t k = od[q];
+                if (k >= 0) od[q] = int32_t(u32(k) < LCAP ? u32(acc[k]) : ld_ag(&cid[k]));
             }
         }
     }
     if (err) atomicOr(ws_ptr<u32>(E, L.ctl) + CTL_ERR, err);
     lds_barrier();                                              // every thread is done with the bitmap
-    for (u32 w = tid; w < WORDS; w += BW) s.bm[w] = 0u;
+    for (u32 w = tid; w < WORDS; w += BW) s.bm[BM_FRONT + w] = 0u;
     lds_barrier();
 }
 
@@ -1789,22 +1951,18 @@ __device__ __forceinline__ Item big_item(const LaunchArgs& a, const u32* s_pref,
 // big, register mode: the modules of the big-module list (above the small kernel's
 // capacity, up to BIG_RCAP digis)
 __global__ __launch_bounds__(B_WG) void k_big(LaunchArgs a) {
-    __shared__ RegModuleSmem<B_WG, K_BIG> s;
+    __shared__ DenseSmem<B_WG, K_BIG> s;
     __shared__ u32 s_pref[MAXB + 1];
     __shared__ u32 s_wsum[B_WG / 64];
     const u32 tid = threadIdx.x;
-    for (u32 w = tid; w < WORDS; w += B_WG) s.bm[w] = 0u;
-    if (tid < CMW) s.cm[tid] = 0u;
+    for (u32 w = tid; w < BM_WORDS; w += B_WG) s.bm[w] = 0u;
     const u32 k = num_events(a);
     const u32 total = event_prefix<B_WG>(a, k, s_pref, s_wsum, CTL_BIG, 1, 0);
     for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
         const Item I = big_item(a, s_pref, k, t, false);
         if (!I.ok) continue;
         const EventDesc E = get_event(a, I.e);
-        const EvLayout L = ev_layout(E.cap, a.n_modules);
-        u32 RC[K_BIG], A[K_BIG];
-        fetch_digis<B_WG, K_BIG>(E, I, tid, RC, A);
-        cluster_regs<B_WG, K_BIG>(a, E, L, I, s, tid, RC, A, [](int) {});
+        cluster_dense<B_WG, K_BIG>(a, E, ev_layout(E.cap, a.n_modules), I, s);
     }
 }
 
@@ -1816,7 +1974,7 @@ __global__ __launch_bounds__(S_WG) void k_scratch(LaunchArgs a) {
     __shared__ u32 s_pref[MAXB + 1];
     __shared__ u32 s_wsum[S_WG / 64];
     const u32 tid = threadIdx.x;
-    for (u32 w = tid; w < WORDS; w += S_WG) s.bm[w] = 0u;
+    for (u32 w = tid; w < BM_WORDS; w += S_WG) s.bm[w] = 0u;
     const u32 k = num_events(a);
     const u32 total = event_prefix<S_WG>(a, k, s_pref, s_wsum, CTL_SCR, 1, 0);
     for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
