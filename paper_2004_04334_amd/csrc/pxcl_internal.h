@@ -166,35 +166,41 @@ struct EvLayout {
     size_t total;
 };
 
+// Every array starts at a multiple of 256 bytes, so the offsets are sums of a few rounded
+// sizes (the kernels compute some of them for every module).
 PXCL_HD constexpr EvLayout ev_layout(u32 N, u32 M) {
     EvLayout L{};
-    size_t o = 0;
-    const size_t n = N, m = M;
-    L.ctl = o;        o = al256(o + CTL_WORDS * 4);
-    L.in_mod = o;     o = al256(o + 2 * n);
-    L.in_row = o;     o = al256(o + 2 * n);
-    L.in_col = o;     o = al256(o + 2 * n);
-    L.in_adc = o;     o = al256(o + 2 * n);
-    L.digi = o;       o = al256(o + 4 * n);
-    L.id = o;         o = al256(o + 4 * n);
-    L.charge = o;     o = al256(o + 4 * n);
-    L.size = o;       o = al256(o + 4 * n);
-    L.tid = o;        o = al256(o + 4 * n);
-    L.tcharge = o;    o = al256(o + 4 * n);
-    L.tsize = o;      o = al256(o + 4 * n);
-    L.mtab = o;       o = al256(o + 16 * m);
-    L.kept = o;       o = al256(o + 4 * m);
-    L.big = o;        o = al256(o + 4 * m);
-    L.scr = o;        o = al256(o + 4 * m);
-    L.present = o;    o = al256(o + 4 * m);
-    L.off = o;        o = al256(o + 4 * m);
-    L.hit_x = o;      o = al256(o + 4 * n);
-    L.hit_y = o;      o = al256(o + 4 * n);
-    L.perm = o;       o = al256(o + 4 * n);
-    L.grp = o;        o = al256(o + 8 * n);
-    L.gcnt = o;       o = al256(o + 4 * m);
-    L.hsum = o;       o = al256(o + 16 * n);
-    L.total = o;
+    const size_t n2 = al256(2 * size_t(N)), n4 = al256(4 * size_t(N)), n8 = al256(8 * size_t(N));
+    const size_t m4 = al256(4 * size_t(M)), m16 = al256(16 * size_t(M));
+    L.ctl = 0;
+    const size_t in = al256(CTL_WORDS * 4);
+    L.in_mod = in;
+    L.in_row = in + n2;
+    L.in_col = in + 2 * n2;
+    L.in_adc = in + 3 * n2;
+    const size_t out = in + 4 * n2;
+    L.digi = out;
+    L.id = out + n4;
+    L.charge = out + 2 * n4;
+    L.size = out + 3 * n4;
+    L.tid = out + 4 * n4;
+    L.tcharge = out + 5 * n4;
+    L.tsize = out + 6 * n4;
+    L.mtab = out + 7 * n4;
+    const size_t mod = L.mtab + m16;
+    L.kept = mod;
+    L.big = mod + m4;
+    L.scr = mod + 2 * m4;
+    L.present = mod + 3 * m4;
+    L.off = mod + 4 * m4;
+    const size_t opt = mod + 5 * m4;
+    L.hit_x = opt;
+    L.hit_y = opt + n4;
+    L.perm = opt + 2 * n4;
+    L.grp = opt + 3 * n4;
+    L.gcnt = opt + 3 * n4 + n8;
+    L.hsum = opt + 3 * n4 + n8 + m4;
+    L.total = L.hsum + al256(16 * size_t(N));
     return L;
 }
 

@@ -118,6 +118,17 @@ __device__ __forceinline__ u32 out_pos(const u32* perm, u32 p) { return perm ? p
 
 // Inclusive scan across the 64 lanes of a wave.
 __device__ __forceinline__ u32 wave_incl_scan(u32 v) {
+#if defined(__AMDGCN__)
+    // six adds with their operand moved between lanes (data-parallel primitives), where
+    // shuffles through the LDS take six round trips
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15, :31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+#else
     const u32 lane = threadIdx.x & 63u;
 #pragma unroll
     for (u32 d = 1; d < 64; d <<= 1) {
@@ -125,6 +136,7 @@ __device__ __forceinline__ u32 wave_incl_scan(u32 v) {
         if (lane >= d) v += y;
     }
     return v;
+#endif
 }
 
 // Exclusive scan over a group of G threads (whole waves).  With G > 64 every thread
@@ -699,21 +711,19 @@ __global__ __launch_bounds__(A_WG) void k_segment(LaunchArgs a) {
 // clustering of one module with its digis in registers (K per thread, group of G)
 // ---------------------------------------------------------------------------
 
-constexpr u32 CMW = (COLS + 31) / 32;   // words of a per-module column mask
-
 template <u32 G, u32 K>
 struct RegModuleSmem {
     static constexpr u32 RCAP = G * K, KBW = RCAP / 32;
-    u32 bm[BM_WORDS];  // fired-pixel bitmap (clear between modules)
-    u32 cm[CMW];       // columns holding a fired pixel (clear between modules)
-    u64 col[COLS + 2]; // entry c+1: column c's run numbers (see col_entry)
-    u64 acc[RCAP];     // per run: parent (16 bits) | size (16) | charge (32), charge and
-                       // size at the roots only; then, at the roots, first pixel (17) |
-                       // size (15) | charge (32)
-    u32 kb[KBW];       // kept-root bits over run index
-    u16 kpre[KBW];     // kept roots before each kb word
+    u32 bm[BM_WORDS];      // fired-pixel bitmap (clear between modules)
+    u16 rpre[BM_WORDS];    // runs before each word, less one when the word's bit 0 continues a
+                           // run of the word above (as in a column's entry, for each word)
+    alignas(8) u64 acc[RCAP];   // per run: parent (16 bits) | size (16) | charge (32), charge and
+                           // size at the roots only; then, at the roots, first pixel (17) |
+                           // size (15) | charge (32)
+    u32 kb[KBW];           // kept-root bits over run index
+    u16 kpre[KBW];         // kept roots before each kb word
     u32 wsum[G / 64];
-    u32 nlink;         // some pair of runs is left to unite
+    u32 nlink;             // some pair of runs is left to unite
 };
 
 // A module as a group sees it.
@@ -764,13 +774,15 @@ __device__ __forceinline__ EventDesc wave_uniform(const EventDesc& E) {
 // meanwhile.
 template <u32 G, u32 K>
 __device__ __forceinline__ void fetch_digis(const EventDesc& E, const Item& I, u32 lt, u32* RC, u32* A) {
+    const u16 *row = (const u16*)E.row + I.st, *col = (const u16*)E.col + I.st, *adc = (const u16*)E.adc + I.st;
 #pragma unroll
     for (u32 q = 0; q < K; ++q) {
         const u32 j = lt + q * G;
-        RC[q] = A[q] = 0u;
+        RC[q] = NOPIX;
+        A[q] = 0u;
         if (q * G < I.n && j < I.n) {
-            RC[q] = u32(E.row[I.st + j]) | (u32(E.col[I.st + j]) << 16);
-            A[q] = E.adc[I.st + j];
+            RC[q] = u32(row[j]) | (u32(col[j]) << 16);
+            A[q] = adc[j];
         }
     }
 }
@@ -793,64 +805,66 @@ __device__ __forceinline__ void for_slots(u32 nq, F f) {
 // one) call it together.  `mid(stage)` runs at the end of phase 1, at the start of phase 3 and after
 // phase 5 (the next module's prefetch).
 //
-// What bounds it is the chain of phases, each an LDS latency or two behind a barrier, so
-// the phases are few (8 barriers) and the LDS reads of a phase do not depend on each other:
+// What bounds it is the number of instructions a wave issues (at four waves per SIMD its
+// vector unit is busy half the time) and, for one module alone, their chain through the
+// phases.  So the phases are few (8 barriers), a digi's LDS reads in a phase do not depend
+// on each other where that can be had, and what is the same for a wave is kept scalar:
 //   1  bitmap
-//   2  run numbers of the columns
+//   2  run numbers of the bitmap words
 //   3  every digi reads the four rows around it in three columns (three pairs of adjacent
-//      words) and the three columns' entries, all at once, and finds its run; a digi that
-//      starts a run stores the run's parent: the run rule B links it to, or itself (a
-//      plain store: no other link decides the first parent)
+//      words) and finds its run; a digi that starts a run stores the run's parent: the run
+//      rule B links it to, or itself (a plain store: no other link decides the first parent)
 //   4  only if some run has a rule A link: those unions
 //   5  root of every digi's run, charge and size into the root's word
 //   6  cut, one bit per kept root
 //   7  outputs
 template <u32 G, u32 K, bool SOLE, typename Mid>
 __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDesc& E, const EvLayout& L,
-                                             const Item& I, RegModuleSmem<G, K>& gp, u32 lt, const u32* RC,
+                                             const Item& I, RegModuleSmem<G, K>& gp, u32 lt, u32* RC,
                                              const u32* A, Mid mid) {
     static_assert(G * K <= 16384, "sizes of up to 15 bits, run numbers of up to 16");
     constexpr u32 KBW = G * K / 32, CPT = (COLS + G - 1) / G;
-    const bool hits = (E.flags & EF_HITS) != 0;
-    u64* hs = ws_ptr<u64>(E, L.hsum);
     const bool act = I.ok;
     const u32 nq = act ? min((I.n + G - 1) / G, K) : 0u;   // slots that may hold a digi
-    u32 err = 0, valid = 0, starts = 0;                    // bit q: slot q holds a pixel, starts its run
+    u32 err = 0, dup = 0, starts = 0;                      // starts, bit q: slot q starts its run
     auto has = [&](u32 mask, u32 q) { return ((mask >> q) & 1u) != 0; };
-    // 1: the module's digis into the bitmap
-    if (lt == 0) gp.nlink = 0u;
+    // 1: the module's digis into the bitmap (RC becomes NOPIX for one out of range)
+    if (lt == 0) {
+        gp.nlink = 0u;
+        gp.acc[0] = 0ull;                                  // run 0, its own root, also when no digi is in range
+    }
     for (u32 w = lt; w < KBW; w += G) gp.kb[w] = 0u;
 #pragma unroll
     for (u32 q = 0; q < K; ++q) {
         if (q < nq && lt + q * G < I.n) {
-            const u32 rq = RC[q] & 0xFFFFu, cq = RC[q] >> 16;
-            if (rq < ROWS && cq < COLS) {
-                const u32 bit = 1u << (rq & 31u);
-                if (atomicOr(&gp.bm[BM_FRONT + cq * WPC + (rq >> 5)], bit) & bit) err |= EB_DUP;
-                atomicOr(&gp.cm[cq >> 5], 1u << (cq & 31u));
-                valid |= 1u << q;
+            const u32 row = RC[q] & 0xFFFFu, c = RC[q] >> 16, bit = 1u << (row & 31u);
+            if (row < ROWS && c < COLS) {
+                dup |= atomicOr(&gp.bm[BM_FRONT + c * WPC + (row >> 5)], bit) & bit;
             } else {
-                err |= EB_RANGE;
+                err = EB_RANGE;
+                RC[q] = NOPIX;
             }
         }
     }
+    if (dup) err |= EB_DUP;
     mid(0);
     gsync<G>();
-    // 2: run starts per word of the columns holding a fired pixel (the only ones whose run
-    // numbers are ever asked for), prefix over them in column order.  A thread takes CPT
+    // 2: run starts per word, prefix over the words in column order.  A thread takes CPT
     // consecutive columns.
     {
-        u64 ent[CPT];
-        u32 cnt = 0, sum[CPT];
+        u32 cnt = 0, n_before[CPT * WPC];
         const u32 c0 = lt * CPT;
 #pragma unroll
         for (u32 i = 0; i < CPT; ++i) {
-            const u32 c = c0 + i;
-            ent[i] = 0ull;
-            sum[i] = NOPIX;
-            if (act && c < COLS && ((gp.cm[c >> 5] >> (c & 31u)) & 1u)) {
-                ent[i] = col_entry(gp.bm, c, sum[i]);
-                cnt += sum[i];
+            u32 above = 0;
+            const u32 c = min(c0 + i, COLS);               // past the last column: words that stay zero
+#pragma unroll
+            for (u32 k = 0; k < WPC; ++k) {
+                const u32 b = gp.bm[BM_FRONT + c * WPC + k];
+                cnt -= b & above;
+                n_before[i * WPC + k] = cnt;
+                cnt += __popc(b & ~(b << 1));
+                above = b >> 31;
             }
         }
         const u32 inc = wave_incl_scan(cnt);
@@ -858,14 +872,14 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
         if constexpr (G > 64) {
             if ((lt & 63u) == 63u) gp.wsum[lt >> 6] = inc;
             gsync<G>();
-            for (u32 i = 0; i < G / 64; ++i) run += i < (lt >> 6) ? gp.wsum[i] : 0u;
+            const u32 wv = wave_uniform(lt >> 6);
+            for (u32 i = 0; i < wv; ++i) run += gp.wsum[i];
         }
 #pragma unroll
         for (u32 i = 0; i < CPT; ++i)
-            if (sum[i] != NOPIX) {
-                gp.col[c0 + i + 1] = ent[i] | run;
-                run += sum[i];
-            }
+            if (c0 + i < COLS)
+#pragma unroll
+                for (u32 k = 0; k < WPC; ++k) gp.rpre[BM_FRONT + (c0 + i) * WPC + k] = u16(run + n_before[i * WPC + k]);
     }
     gsync<G>();
     mid(1);
@@ -874,31 +888,33 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
     u32 link = 0;                                          // bit q: slot q has a rule A link
     for_slots<K, 2>(nq, [&](u32 q) {
         X[q] = 0u;
-        if (!has(valid, q)) return;
+        if (RC[q] == NOPIX) return;
         const u32 row = RC[q] & 0xFFFFu, c = RC[q] >> 16;
         // rows s..s+3 of the columns c-1, c, c+1 lie in two adjacent words each
-        const u32 s = row >= 2 ? row - 2 : 0u, ks = s >> 5;
-        const u32* w = &gp.bm[BM_FRONT + c * WPC + ks - WPC];
+        const u32 s = row >= 2 ? row - 2 : 0u, ks = s >> 5, w0 = c * WPC + ks;   // in column c-1
+        const u32* w = &gp.bm[w0];
         const u32 l0 = w[0], l1 = w[1], m0 = w[WPC], m1 = w[WPC + 1], r0 = w[2 * WPC], r1 = w[2 * WPC + 1];
-        const u64 el = gp.col[c], em = gp.col[c + 1], er = gp.col[c + 2];
+        const u32 own = (row >> 5) - ks, before = gp.rpre[w0 + WPC + own];
         // bit i: row - 2 + i fired (above the first row and below the last one: not)
         const u32 up = row >= 2 ? 0u : 2u - row, mask = row + 1 < ROWS ? 15u : 7u;
         auto window = [&](u32 lo, u32 hi) { return (u32(((u64(hi) << 32) | lo) >> (s & 31u)) << up) & mask; };
+        auto run_in = [&](u32 before, u32 word, u32 r) {   // run of row r, fired, of a word
+            return before + __popc(word & ~(word << 1) & ((2u << (r & 31u)) - 1u)) - 1u;
+        };
         const u32 wl = window(l0, l1), wm = window(m0, m1), wr = window(r0, r1);
-        const u32 kr = row >> 5;
-        const u32 r = run_number(em, kr, kr == ks ? m0 : m1, row);
+        const u32 r = run_in(before, own ? m1 : m0, row);
         X[q] = r;
         if (wm & 2u) return;                               // not the first pixel of its run
         starts |= 1u << q;
         u32 parent = r;
         if (wl & 14u) {                                    // rule B
-            const u32 f = row - 1u + __builtin_ctz((wl >> 1) & 7u), kf = f >> 5;
-            parent = run_number(el, kf, kf == ks ? l0 : l1, f);
+            const u32 f = row - 1u + __builtin_ctz((wl >> 1) & 7u), h = (f >> 5) - ks;
+            parent = run_in(gp.rpre[w0 + h], h ? l1 : l0, f);
         }
         gp.acc[r] = u64(parent) << 48;
         if ((wr & 2u) && ((wm | wr) & 1u)) {               // rule A
-            const u32 f = row - 1u, kf = f >> 5;
-            X[q] |= run_number(er, kf, kf == ks ? r0 : r1, f) << 16;
+            const u32 f = row - 1u, h = (f >> 5) - ks;
+            X[q] |= run_in(gp.rpre[w0 + 2 * WPC + h], h ? r1 : r0, f) << 16;
             link |= 1u << q;
         }
     });
@@ -907,37 +923,41 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
     // 4: rule A's unions (groups that share the workgroup's barrier all take it)
     const bool unions = ld_wg(&gp.nlink) != 0;
     if (unions) {
-#pragma unroll
-        for (u32 q = 0; q < K; ++q)
+#pragma unroll 1
+        for (u32 q = 0; q < nq; ++q)
             if (has(link, q)) unite_packed(gp.acc, X[q] & 0xFFFFu, X[q] >> 16);
     }
     if ((G > 64 && !SOLE) || unions) gsync<G>();
-    // 5: roots (the walks of all slots step together; each store points a run to one of its
-    // ancestors), then charge and size per root.  Sums touch the low 48 bits of roots only,
-    // walks read the parents and write those of other runs.
+    // 5: roots (the walks of all slots step together), then charge and size per root.  Sums
+    // touch the low 48 bits of roots only, walks read the parents.  Most trees are shallow:
+    // a few plain steps; what is left points runs to ancestors as it goes.
+    u32 more = 0;
 #pragma unroll
-    for (u32 q = 0; q < K; ++q) X[q] &= 0xFFFFu;
-    u32 todo = valid;
-    for (u32 it = 0; todo && it < 2 * MAX_RUNS; ++it) {
-        u32 P[K];
+    for (u32 q = 0; q < K; ++q)
+        if (q < nq) {
+            X[q] &= 0xFFFFu;                               // run 0 where there is no pixel
+            const u32 p = parent_of(gp.acc, X[q]);
+            if (p != X[q]) starts &= ~(1u << q);           // now: the digi starts its cluster
+            X[q] = p;
+        }
+    for (u32 step = 0; step < 3; ++step) {
+        more = 0;
 #pragma unroll
         for (u32 q = 0; q < K; ++q)
-            if (q < nq && has(todo, q)) P[q] = parent_of(gp.acc, X[q]);
-#pragma unroll
-        for (u32 q = 0; q < K; ++q)
-            if (q < nq && has(todo, q)) {
-                const u32 g = parent_of(gp.acc, P[q]);
-                if (P[q] != X[q]) starts &= ~(1u << q);    // now: the digi starts its cluster
-                if (g == P[q]) todo &= ~(1u << q);
-                else st_wg(hi_word(gp.acc, X[q]), g << 16);
-                X[q] = g;
+            if (q < nq) {
+                const u32 p = parent_of(gp.acc, X[q]);
+                more |= p ^ X[q];
+                X[q] = p;
             }
+        if (!more) break;
+    }
+    if (more) {
+#pragma unroll 1
+        for (u32 q = 0; q < nq; ++q) X[q] = find_packed(gp.acc, X[q]);
     }
 #pragma unroll
     for (u32 q = 0; q < K; ++q)
-        if (q < nq && has(valid, q)) {
-            atomicAdd(&gp.acc[X[q]], (1ull << 32) | u64(A[q] & 0xFFFFu));
-        }
+        if (q < nq && RC[q] != NOPIX) atomicAdd(&gp.acc[X[q]], (1ull << 32) | u64(A[q] & 0xFFFFu));
     mid(2);
     gsync<G>();
     // 6: charge cut, one bit per kept root; its word's upper half becomes the first pixel
@@ -978,41 +998,42 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
             return u32(__hip_atomic_load(&gp.kpre[r >> 5], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) +
                    __popc(gp.kb[r >> 5] & ((1u << (r & 31u)) - 1u));
         };
-        int32_t* tid_ = ws_ptr<int32_t>(E, L.tid);
-        int32_t* tch = ws_ptr<int32_t>(E, L.tcharge);
-        int32_t* tsz = ws_ptr<int32_t>(E, L.tsize);
-        int32_t* od = (int32_t*)E.o_digi;
+        const bool hits = (E.flags & EF_HITS) != 0;
+        u64* hs = ws_ptr<u64>(E, L.hsum) + 2 * size_t(I.st);
+        int32_t* tid_ = ws_ptr<int32_t>(E, L.tid) + I.st;
+        int32_t* tch = ws_ptr<int32_t>(E, L.tcharge) + I.st;
+        int32_t* tsz = ws_ptr<int32_t>(E, L.tsize) + I.st;
         const u32* perm = perm_of(E, L);
+        int32_t* od = (int32_t*)E.o_digi + (perm ? 0u : I.st);
         const u32 idbase = I.mod * PIX;
 #pragma unroll
         for (u32 q = 0; q < K; ++q) {
             const u32 j = lt + q * G;
             if (q < nq && j < I.n) {
                 int32_t id = -1;
-                if (has(valid, q)) {
+                if (RC[q] != NOPIX) {
                     const u64 v = gp.acc[X[q]];
                     const u32 charge = u32(v), row = RC[q] & 0xFFFFu, c = RC[q] >> 16;
-                    const bool keep = charge >= a.charge_cut;
-                    if (keep) id = int32_t(idbase + u32(v >> 47));
-                    if (keep && (hits || has(starts, q))) {
-                        const u32 p = I.st + position(X[q]);
+                    st_wg(&gp.bm[BM_FRONT + c * WPC + (row >> 5)], 0u);   // several digis may share a word
+                    if (charge >= a.charge_cut) {
+                        id = int32_t(idbase + u32(v >> 47));
                         if (has(starts, q)) {
+                            const u32 p = position(X[q]);
                             tid_[p] = id;
                             tch[p] = int32_t(charge);
                             tsz[p] = int32_t(u32(v >> 32) & 0x7FFFu);
                         }
                         if (hits) {
+                            const u32 p = position(X[q]);
                             const u64 w = A[q] & 0xFFFFu;
                             atomicAdd(&hs[2 * p], w * c);
                             atomicAdd(&hs[2 * p + 1], w * row);
                         }
                     }
-                    st_wg(&gp.bm[BM_FRONT + c * WPC + (row >> 5)], 0u);   // several digis may share a word
                 }
-                od[out_pos(perm, I.st + j)] = id;
+                od[perm ? perm[I.st + j] : j] = id;
             }
         }
-        if (lt < CMW) gp.cm[lt] = 0u;
         if (err) atomicOr(ws_ptr<u32>(E, L.ctl) + CTL_ERR, err);
     }
     gsync<G>();
@@ -1069,16 +1090,28 @@ __device__ __forceinline__ void narrow_window(u32& lo, u32& hi, u64 ge, long lon
     }
 }
 
-__device__ __forceinline__ void module_range(const EventDesc& E, u32 n_modules, u32 key, u32 lane, u32& first,
-                                             u32& end) {
+// The search in three steps, each issuing the loads the next one looks at, so that a group
+// can do other work in between: probe, narrow, finish.
+struct RangeSearch {
+    u32 v;                       // probe
+    u32 lo0, hi0, lo1, hi1;      // each answer lies in [lo, hi]
+    u32 p0, q0, p1, q1;          // last candidates (ids), NOPIX past hi
+};
+// Index where module `key` starts if the modules are evenly filled (any guess will do).
+__device__ __forceinline__ long long range_guess(const EventDesc& E, u32 n_modules, u32 key) {
+    return static_cast<long long>(float(key) * (float(E.n) / float(n_modules)));
+}
+__device__ __forceinline__ void range_probe(RangeSearch& S, const EventDesc& E, u32 n_modules, u32 key, u32 lane) {
+    const long long n = E.n, p = range_guess(E, n_modules, key) + (static_cast<long long>(lane) - 32) * SEARCH_STEP;
+    S.v = ((const u16*)E.module)[p < 0 ? 0u : u32(p >= n ? n - 1 : p)];
+}
+__device__ __forceinline__ void range_narrow(RangeSearch& S, const EventDesc& E, u32 n_modules, u32 key, u32 lane) {
     const u16* mod = (const u16*)E.module;
     const u32 n = E.n;
-    u32 lo0 = 0, hi0 = n, lo1 = 0, hi1 = n;       // each answer lies in [lo, hi]
+    const long long guess = range_guess(E, n_modules, key);
+    u32 lo0 = 0, hi0 = n, lo1 = 0, hi1 = n;
     {
-        const long long guess = static_cast<long long>((u64(key) * n) / n_modules);
-        const long long p = guess + (static_cast<long long>(lane) - 32) * SEARCH_STEP;
-        const u32 v = mod[p < 0 ? 0 : (p >= (long long)n ? n - 1 : u32(p))];
-        const u64 b0 = __ballot(v >= key), b1 = __ballot(v >= key + 1);
+        const u64 b0 = __ballot(S.v >= key), b1 = __ballot(S.v >= key + 1);
         narrow_window(lo0, hi0, b0, guess, n);
         narrow_window(lo1, hi1, b1, guess, n);
     }
@@ -1092,14 +1125,20 @@ __device__ __forceinline__ void module_range(const EventDesc& E, u32 n_modules, 
         if (w0) narrow_range(lo0, hi0, b0);
         if (w1) narrow_range(lo1, hi1, b1);
     }
+    S.lo0 = lo0; S.hi0 = hi0; S.lo1 = lo1; S.hi1 = hi1;
     // at most SEARCH_LAST = 128 candidates per bound: positions lo + lane, lo + 64 + lane
-    const bool g0 = lo0 + lane < hi0 && mod[lo0 + lane] >= key;
-    const bool h0 = lo0 + 64 + lane < hi0 && mod[lo0 + 64 + lane] >= key;
-    const bool g1 = lo1 + lane < hi1 && mod[lo1 + lane] >= key + 1;
-    const bool h1 = lo1 + 64 + lane < hi1 && mod[lo1 + 64 + lane] >= key + 1;
-    const u64 b0 = __ballot(g0), c0 = __ballot(h0), b1 = __ballot(g1), c1 = __ballot(h1);
-    first = b0 ? lo0 + u32(__builtin_ctzll(b0)) : c0 ? lo0 + 64 + u32(__builtin_ctzll(c0)) : hi0;
-    end = b1 ? lo1 + u32(__builtin_ctzll(b1)) : c1 ? lo1 + 64 + u32(__builtin_ctzll(c1)) : hi1;
+    S.p0 = S.q0 = S.p1 = S.q1 = NOPIX;
+    if (lo0 + lane < hi0) S.p0 = mod[lo0 + lane];
+    if (lo0 + 64 + lane < hi0) S.q0 = mod[lo0 + 64 + lane];
+    if (lo1 + lane < hi1) S.p1 = mod[lo1 + lane];
+    if (lo1 + 64 + lane < hi1) S.q1 = mod[lo1 + 64 + lane];
+}
+__device__ __forceinline__ void range_finish(const RangeSearch& S, u32 key, u32& first, u32& end) {
+    auto at_least = [](u32 v, u32 k) { return v != NOPIX && v >= k; };
+    const u64 b0 = __ballot(at_least(S.p0, key)), c0 = __ballot(at_least(S.q0, key));
+    const u64 b1 = __ballot(at_least(S.p1, key + 1)), c1 = __ballot(at_least(S.q1, key + 1));
+    first = b0 ? S.lo0 + u32(__builtin_ctzll(b0)) : c0 ? S.lo0 + 64 + u32(__builtin_ctzll(c0)) : S.hi0;
+    end = b1 ? S.lo1 + u32(__builtin_ctzll(b1)) : c1 ? S.lo1 + 64 + u32(__builtin_ctzll(c1)) : S.hi1;
 }
 
 // Order and range checks of every digi's module id (launches without the
@@ -1142,7 +1181,7 @@ struct SmallSmem {
     RegModuleSmem<G, K> grp[MPW];
     u32 pref[MAXB + 1];
     u32 wsum[WG / 64];
-    u32 tick[2];
+    u32 tick;                                 // the module after the current one (G > 64), once it is dynamic
 };
 
 // Waves per SIMD the shape's LDS allows, at most four (at most 128 registers):
@@ -1167,7 +1206,6 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     const u32 gofs = WAVE ? 0u : g;
     RegModuleSmem<G, K>& gp = s.grp[g];
     for (u32 w = lt; w < BM_WORDS; w += G) gp.bm[w] = 0u;
-    if (lt < CMW) gp.cm[lt] = 0u;
     const u32 k = num_events(a);
     // Without the segmentation kernel (one event): every module is a unit, its
     // digis found by search; this kernel then checks the module ids, writes the
@@ -1197,36 +1235,62 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     } else {
         total = event_prefix<WG>(a, k, s.pref, s.wsum, CNT_UNITS, 1, 0);
     }
-    // Work unit t: unit t - pref[e] of event e, and its module's table entry.
-    auto entry_of = [&](u32 t, EventDesc& Ev, u32& e, u32& mod) -> ModRange {
-        e = k == 1 ? 0u : find_slot(s.pref, k, t);
-        Ev = get_event(a, e);
-        const EvLayout L = ev_layout(Ev.cap, a.n_modules);
-        if (fused) {
-            mod = t;
-            u32 f, en;
-            module_range(Ev, a.n_modules, mod, lt & 63u, f, en);
-            const u64 tag = u64(Ev.epoch) << 32;
-            const ModRange r{tag | f, tag | en};
-            if (lt == 0 && en > f) ws_ptr<ModRange>(Ev, L.mtab)[mod] = r;   // for the big kernel, compaction, hits
-            return r;
+    // Work unit t: unit t - pref[e] of event e.  Its module's range comes in three steps,
+    // each issuing the loads the next one waits for: the module id, the module's table entry,
+    // the item (without the table: the steps of the search).
+    struct Next {
+        EventDesc E;
+        u32 e, mod;
+        RangeSearch S;
+        ModRange r;
+    };
+    const u32 lane = lt & 63u;
+    auto step_module = [&](u32 t, Next& N) {
+        N.e = 0;
+        if (k > 1) {                          // the last event whose first unit is at or before t
+            const u32 in0 = lane < k && s.pref[lane] <= t, in1 = lane + 64 < k && s.pref[lane + 64] <= t;
+            N.e = wave_uniform(u32(__popcll(__ballot(in0)) + __popcll(__ballot(in1))) - 1u);
         }
-        mod = unit_module(a, Ev, L, s.pref[e + 1] - s.pref[e], t - s.pref[e]);
-        return ws_ptr<const ModRange>(Ev, L.mtab)[mod];
+        N.E = get_event(a, N.e);
+        if (fused) {
+            N.mod = t;
+            range_probe(N.S, N.E, a.n_modules, t, lane);
+            return;
+        }
+        const u32 first = wave_uniform(s.pref[N.e]), units = wave_uniform(s.pref[N.e + 1]) - first;
+        N.mod = t - first;                    // dense (a list as long as the module count is all of them)
+        if (units != a.n_modules) N.mod = ws_ptr<const u32>(N.E, ev_layout(N.E.cap, a.n_modules).present)[t - first];
+    };
+    auto step_range = [&](Next& N) {
+        if (fused) {
+            range_narrow(N.S, N.E, a.n_modules, N.mod, lane);
+            return;
+        }
+        N.mod = min(wave_uniform(N.mod), a.n_modules - 1);
+        N.r = ws_ptr<const ModRange>(N.E, ev_layout(N.E.cap, a.n_modules).mtab)[N.mod];
     };
     // I.n = 0 for an entry that is not this launch's (or inconsistent after an
     // ordering error); ok only for a present module the group can hold.
-    auto make_item = [&](const ModRange& r, const EventDesc& Ev, u32 e, u32 mod, bool valid) {
-        Item I{e, mod, 0, 0, mod, false};
-        if (valid && u32(r.first >> 32) == Ev.epoch && u32(r.end >> 32) == Ev.epoch) {
-            const u32 st = u32(r.first), en = u32(r.end);
-            if (st < en && en <= Ev.n) {
-                I.st = st;
-                I.n = en - st;
-            }
+    auto step_item = [&](Next& N) {
+        Item I{N.e, N.mod, 0, 0, N.mod, false};
+        u32 st, en;
+        bool mine = true;
+        if (fused) {
+            range_finish(N.S, N.mod, st, en);
+            const u64 tag = u64(N.E.epoch) << 32;
+            if (lt == 0 && en > st)           // for the big kernel, compaction, hits
+                ws_ptr<ModRange>(N.E, ev_layout(N.E.cap, a.n_modules).mtab)[N.mod] = ModRange{tag | st, tag | en};
+        } else {
+            st = u32(N.r.first);
+            en = u32(N.r.end);
+            mine = u32(N.r.first >> 32) == N.E.epoch && u32(N.r.end >> 32) == N.E.epoch;
+        }
+        if (mine && st < en && en <= N.E.n) {
+            I.st = st;
+            I.n = en - st;
         }
         I.ok = I.n > 0 && I.n <= G * K;
-        return I;
+        return wave_uniform(I);               // one module per wave (or per group of waves)
     };
     // A module larger than the group goes to the big-module list, or above BIG_RCAP
     // digis to the scratch-mode list (or, when that kernel is not launched, keeps
@@ -1255,79 +1319,72 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     // next is drawn while the current one is clustered, and the next module's
     // table entry (or range, by search) and digis are loaded meanwhile.
     const u32 per_round = gridDim.x * MPW;
-    u32 base = xcd_order(blockIdx.x, gridDim.x) * MPW + (WAVE ? g : 0u);
+    u32 base = xcd_order(blockIdx.x, gridDim.x) * MPW + (WAVE ? wave_uniform(g) : 0u);
+    const u32 ofs = wave_uniform(gofs);
     EventDesc E{};
     Item I{0, 0, 0, 0, 0, false};
     u32 RC[K], A[K];
-    {
-        const u32 t = base + gofs;
-        if (t < total) {
-            u32 e, mod;
-            const ModRange r = entry_of(t, E, e, mod);
-            I = make_item(r, E, e, mod, true);
-        }
-        I = wave_uniform(I);                      // one module per wave (or per group of waves)
-        E = wave_uniform(E);
+    if (base + ofs < total) {
+        Next N{};
+        step_module(base + ofs, N);
+        step_range(N);
+        I = step_item(N);
+        E = N.E;
         if (I.ok) fetch_digis<G, K>(E, I, lt, RC, A);
     }
     if (fused) id_check_finish<WG>(a, get_event(a, 0), idc);
-    const u32 nrounds = per_round < total ? max(1u, u32((3ull * total) / (4ull * per_round))) : 1u;   // static
+    // (units of a launch: at most MAXB * PXCL_MAX_MODULES, so three times that fits 32 bits)
+    const u32 nrounds = per_round < total ? max(1u, 3u * total / (4u * per_round)) : 1u;   // static
     const u32 nstatic = nrounds * per_round;
     const bool dyn = nstatic < total;             // tickets needed at all
+    const bool drawer = WAVE ? lt == 0 : tid == 0;
     u32 round = 0;                                // round of the current module (>= nrounds: dynamic)
     u32 nv = total;                               // ticket of the next dynamic module (in flight)
-    if (dyn && nrounds == 1 && ((WAVE && lt == 0) || (!WAVE && tid == 0))) nv = atomicAdd(ticket(a), STEP) + nstatic;
+    if (dyn && nrounds == 1) {
+        if (drawer) nv = atomicAdd(ticket(a), STEP) + nstatic;
+        if constexpr (!WAVE) {                    // every wave reads it at its first module's first stage
+            if (tid == 0) s.tick = nv;
+            lds_barrier();
+        }
+    }
 
     while (base < total) {
-        u32 nbase = total, nv2 = 0, ne = 0, nmod = 0;
-        EventDesc En{};
+        u32 nbase = total, nv2 = total;
+        Next N{};
         bool have = false;
-        ModRange ent{0, 0};
         Item In{0, 0, 0, 0, 0, false};
         u32 NRC[K], NA[K];
-        auto issue_entry = [&]() {
-            const u32 t = nbase + gofs;
-            if (t < total) {
-                ent = entry_of(t, En, ne, nmod);  // a table load: issued here, used at stage 2
-                have = true;
-            }
-        };
         auto mid = [&](int stage) {
             if (stage == 0) {
                 const bool snext = round + 1 < nrounds;            // next module static
                 const bool draw = dyn && round + 2 >= nrounds;     // module after next dynamic
-                if constexpr (WAVE) {
-                    nbase = snext ? base + per_round : __builtin_amdgcn_readfirstlane(nv);
-                    nv2 = total;
-                    if (draw && lt == 0 && nbase < total) nv2 = atomicAdd(ticket(a), 1u) + nstatic;
-                    issue_entry();
-                } else if (tid == 0) {
-                    const u32 nx = snext ? base + per_round : nv;
-                    s.tick[1] = nx;
-                    nv2 = (draw && nx < total) ? atomicAdd(ticket(a), STEP) + nstatic : total;
-                }
+                if (snext) nbase = base + per_round;
+                else if (dyn) nbase = WAVE ? wave_uniform(nv) : wave_uniform(s.tick);
+                if (draw && drawer && nbase < total) nv2 = atomicAdd(ticket(a), STEP) + nstatic;
+                have = nbase + ofs < total;
+                if (have) step_module(nbase + ofs, N);
             } else if (stage == 1) {
-                if constexpr (!WAVE) {
-                    nbase = s.tick[1];
-                    issue_entry();
+                if (have) step_range(N);
+            } else {
+                // the drawn ticket, for the stage 0 of the next module (barriers lie between)
+                if constexpr (!WAVE)
+                    if (tid == 0) s.tick = nv2;
+                if (have) {
+                    In = step_item(N);
+                    if (In.ok) fetch_digis<G, K>(N.E, In, lt, NRC, NA);
                 }
-            } else if (stage == 2) {
-                In = wave_uniform(make_item(ent, En, ne, nmod, have));
-                En = wave_uniform(En);
-                if (In.ok) fetch_digis<G, K>(En, In, lt, NRC, NA);
             }
         };
-        if (base + gofs < total && !I.ok && lt == 0) skip(E, I);
+        if (base + ofs < total && !I.ok && lt == 0) skip(E, I);
         if (!WAVE || I.ok) {
-            const EvLayout L = ev_layout(E.cap, a.n_modules);
-            cluster_regs<G, K, MPW == 1>(a, E, L, I, gp, lt, RC, A, mid);
+            cluster_regs<G, K, MPW == 1>(a, E, ev_layout(E.cap, a.n_modules), I, gp, lt, RC, A, mid);
         } else {
             mid(0);
             mid(1);
             mid(2);
         }
         base = nbase;
-        E = En;
+        E = N.E;
         I = In;
         nv = nv2;
         ++round;
