@@ -55,10 +55,11 @@ enum : u32 {
                       // launch parity (EventDesc::slot); a launch clears the other one
     CTL_DEFERRED = 7, // 1: a batch launch with LF_DEFER left this event to its second
                       // launch (set by the compaction, cleared by segmentation or grouping)
-    CTL_CTR = 8,      // launch counters when the event is launched on its own
+    CTL_CTR = 8,      // launch counters when the event is launched on its own; in a batch the
+                      // first is one of the small kernel's tickets (zero between launches)
     CTL_WORDS = 64
 };
-// Launch counters: the small-module kernel's ticket.
+// Launch counters: the small-module kernel's ticket (when it needs only one).
 enum : u32 { S_TICK = 0, N_CTR = 8 };
 // Host status block (pinned) written by the compaction kernel.
 enum : u32 { HS_EPOCH = 0, HS_ERR = 1, HS_NCL = 2, HS_WORDS = 16 };

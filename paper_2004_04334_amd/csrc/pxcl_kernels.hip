@@ -98,12 +98,19 @@ __device__ __forceinline__ void gsync() {
 __device__ __forceinline__ void lds_barrier() { gsync<128>(); }
 
 __device__ __forceinline__ u32 num_events(const LaunchArgs& a) { return a.hdr ? a.hdr[0] : 1u; }
-__device__ __forceinline__ EventDesc get_event(const LaunchArgs& a, u32 e) {
-    // the header is not written while a kernel runs: with e the same for a whole wave its
-    // fields come by scalar loads
-    const EventDesc* d = (const EventDesc*)(const EventDesc PXCL_C*)(reinterpret_cast<uintptr_t>(a.hdr) + HDR_EV_OFFSET);
-    return a.hdr ? d[e] : a.single;
+// Event e of the launch, in the header or in the kernel's own argument.  Neither is written
+// while a kernel runs, so both are constant memory: with e the same for a whole wave the
+// fields come by scalar loads, where they are needed.
+__device__ __forceinline__ const EventDesc* event_at(const LaunchArgs& a, u32 e) {
+#if defined(__AMDGCN__)
+    const u8 PXCL_C* single = (const u8 PXCL_C*)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(LaunchArgs, single);
+#else
+    const u8* single = reinterpret_cast<const u8*>(&a.single);
+#endif
+    const u8 PXCL_C* d = (const u8 PXCL_C*)(reinterpret_cast<uintptr_t>(a.hdr) + HDR_EV_OFFSET + sizeof(EventDesc) * e);
+    return (const EventDesc*)(const EventDesc PXCL_C*)(a.hdr ? d : single);
 }
+__device__ __forceinline__ EventDesc get_event(const LaunchArgs& a, u32 e) { return *event_at(a, e); }
 __device__ __forceinline__ u32* ticket(const LaunchArgs& a) { return (u32*)(a.ctr + S_TICK); }
 template <typename T>
 __device__ __forceinline__ T* ws_ptr(const EventDesc& E, size_t off) {
@@ -554,6 +561,7 @@ __global__ __launch_bounds__(G_WG) void k_group_table(LaunchArgs a) {
             ctl[CTL_BIG] = 0u;
             ctl[CTL_SCR] = 0u;
             ctl[CTL_DEFERRED] = 0u;
+            ctl[CTL_CTR] = 0u;                   // the small kernel's ticket of this event
             ctl[CTL_PRESENT + slot] = pcarry;
             ctl[CTL_PRESENT + (slot ^ 1u)] = 0u;
         }
@@ -662,6 +670,7 @@ __global__ __launch_bounds__(A_WG) void k_segment(LaunchArgs a) {
                 ctl[CTL_BIG] = 0u;
                 ctl[CTL_SCR] = 0u;
                 ctl[CTL_DEFERRED] = 0u;
+                ctl[CTL_CTR] = 0u;                     // the small kernel's ticket of this event
                 ctl[CTL_PRESENT + (slot ^ 1u)] = 0u;   // for the next launch (the last one's is done)
             }
             u32* kept = ws_ptr<u32>(E, L.kept);
@@ -820,8 +829,8 @@ __device__ __forceinline__ void for_slots(u32 nq, F f) {
 //   7  outputs
 template <u32 G, u32 K, bool SOLE, typename Mid>
 __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDesc& E, const EvLayout& L,
-                                             const Item& I, RegModuleSmem<G, K>& gp, u32 lt, u32* RC,
-                                             const u32* A, Mid mid) {
+                                             const Item& I, RegModuleSmem<G, K>& gp, u32 lt, u32* RC, u32* A,
+                                             Mid mid) {
     static_assert(G * K <= 16384, "sizes of up to 15 bits, run numbers of up to 16");
     constexpr u32 KBW = G * K / 32, CPT = (COLS + G - 1) / G;
     const bool act = I.ok;
@@ -1025,7 +1034,7 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
                         }
                         if (hits) {
                             const u32 p = position(X[q]);
-                            const u64 w = A[q] & 0xFFFFu;
+                            const u64 w = E.adc[I.st + j];             // A holds the next module's
                             atomicAdd(&hs[2 * p], w * c);
                             atomicAdd(&hs[2 * p + 1], w * row);
                         }
@@ -1184,13 +1193,14 @@ struct SmallSmem {
     u32 tick;                                 // the module after the current one (G > 64), once it is dynamic
 };
 
-// Waves per SIMD the shape's LDS allows, at most four (at most 128 registers):
-// modules in flight bound throughput, so registers should not bound them first.
+// Waves per SIMD the shape's LDS allows, at most five (at most 96 registers): modules in
+// flight bound throughput, so registers should not bound them first.  At 256x1 five fit
+// (LDS for five groups a compute unit); six at 512x1 would spill 26 registers a lane.
 template <u32 WG, u32 MPW, u32 K>
 constexpr u32 small_waves_per_simd() {
     constexpr u32 lds_groups = 163840u / u32(sizeof(SmallSmem<WG, MPW, K>));
     constexpr u32 w = lds_groups * (WG / 64) / 4;
-    return w < 1 ? 1 : (w > 4 ? 4 : w);
+    return w < 1 ? 1 : (w > 5 ? 5 : w);
 }
 #ifndef PXCL_WAVES_PER_EU
 #define PXCL_WAVES_PER_EU(...) __attribute__((amdgpu_waves_per_eu(__VA_ARGS__)))
@@ -1239,7 +1249,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     // each issuing the loads the next one waits for: the module id, the module's table entry,
     // the item (without the table: the steps of the search).
     struct Next {
-        EventDesc E;
+        const EventDesc* E;
         u32 e, mod;
         RangeSearch S;
         ModRange r;
@@ -1251,23 +1261,23 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
             const u32 in0 = lane < k && s.pref[lane] <= t, in1 = lane + 64 < k && s.pref[lane + 64] <= t;
             N.e = wave_uniform(u32(__popcll(__ballot(in0)) + __popcll(__ballot(in1))) - 1u);
         }
-        N.E = get_event(a, N.e);
+        N.E = event_at(a, N.e);
         if (fused) {
             N.mod = t;
-            range_probe(N.S, N.E, a.n_modules, t, lane);
+            range_probe(N.S, *N.E, a.n_modules, t, lane);
             return;
         }
         const u32 first = wave_uniform(s.pref[N.e]), units = wave_uniform(s.pref[N.e + 1]) - first;
         N.mod = t - first;                    // dense (a list as long as the module count is all of them)
-        if (units != a.n_modules) N.mod = ws_ptr<const u32>(N.E, ev_layout(N.E.cap, a.n_modules).present)[t - first];
+        if (units != a.n_modules) N.mod = ws_ptr<const u32>(*N.E, ev_layout(N.E->cap, a.n_modules).present)[t - first];
     };
     auto step_range = [&](Next& N) {
         if (fused) {
-            range_narrow(N.S, N.E, a.n_modules, N.mod, lane);
+            range_narrow(N.S, *N.E, a.n_modules, N.mod, lane);
             return;
         }
         N.mod = min(wave_uniform(N.mod), a.n_modules - 1);
-        N.r = ws_ptr<const ModRange>(N.E, ev_layout(N.E.cap, a.n_modules).mtab)[N.mod];
+        N.r = ws_ptr<const ModRange>(*N.E, ev_layout(N.E->cap, a.n_modules).mtab)[N.mod];
     };
     // I.n = 0 for an entry that is not this launch's (or inconsistent after an
     // ordering error); ok only for a present module the group can hold.
@@ -1277,15 +1287,15 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
         bool mine = true;
         if (fused) {
             range_finish(N.S, N.mod, st, en);
-            const u64 tag = u64(N.E.epoch) << 32;
+            const u64 tag = u64(N.E->epoch) << 32;
             if (lt == 0 && en > st)           // for the big kernel, compaction, hits
-                ws_ptr<ModRange>(N.E, ev_layout(N.E.cap, a.n_modules).mtab)[N.mod] = ModRange{tag | st, tag | en};
+                ws_ptr<ModRange>(*N.E, ev_layout(N.E->cap, a.n_modules).mtab)[N.mod] = ModRange{tag | st, tag | en};
         } else {
             st = u32(N.r.first);
             en = u32(N.r.end);
-            mine = u32(N.r.first >> 32) == N.E.epoch && u32(N.r.end >> 32) == N.E.epoch;
+            mine = u32(N.r.first >> 32) == N.E->epoch && u32(N.r.end >> 32) == N.E->epoch;
         }
-        if (mine && st < en && en <= N.E.n) {
+        if (mine && st < en && en <= N.E->n) {
             I.st = st;
             I.n = en - st;
         }
@@ -1314,14 +1324,19 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     };
 
     // Modules are assigned statically in rounds (round r: module r*per_round + the
-    // group's index) for about three quarters of the work, the rest comes from a
-    // ticket counter, which every group contends for.  The ticket of the module after
-    // next is drawn while the current one is clustered, and the next module's
-    // table entry (or range, by search) and digis are loaded meanwhile.
+    // group's index) for about three quarters of the work, the rest by ticket.  The ticket of
+    // the module after next is drawn while the current one is clustered, and the next
+    // module's table entry (or range, by search) and digis are loaded meanwhile.
+    // Draws from one counter are served one after another, ~15 ns each, and all groups draw
+    // their first one together: with one counter for 1,280 groups every first module of a
+    // 16-event launch took 20-30 us instead of 6-10.  So the groups and the modules left are
+    // dealt out to one counter per event (each in its event's control words), with at least
+    // 16 groups at each.  One event has one counter, used only from three static rounds on:
+    // with fewer, what a draw costs is more than what it balances.
     const u32 per_round = gridDim.x * MPW;
     u32 base = xcd_order(blockIdx.x, gridDim.x) * MPW + (WAVE ? wave_uniform(g) : 0u);
     const u32 ofs = wave_uniform(gofs);
-    EventDesc E{};
+    const EventDesc* E = event_at(a, 0);
     Item I{0, 0, 0, 0, 0, false};
     u32 RC[K], A[K];
     if (base + ofs < total) {
@@ -1330,18 +1345,22 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
         step_range(N);
         I = step_item(N);
         E = N.E;
-        if (I.ok) fetch_digis<G, K>(E, I, lt, RC, A);
+        if (I.ok) fetch_digis<G, K>(*E, I, lt, RC, A);
     }
     if (fused) id_check_finish<WG>(a, get_event(a, 0), idc);
     // (units of a launch: at most MAXB * PXCL_MAX_MODULES, so three times that fits 32 bits)
-    const u32 nrounds = per_round < total ? max(1u, 3u * total / (4u * per_round)) : 1u;   // static
+    u32 nrounds = per_round < total ? max(1u, 3u * total / (4u * per_round)) : 1u;         // static
+    if (k == 1 && nrounds < 3) nrounds = (total + per_round - 1) / per_round;              // all of them
     const u32 nstatic = nrounds * per_round;
+    const u32 parts = k == 1 ? 1u : max(1u, min(k, gridDim.x * (WAVE ? MPW : 1u) / 16u)), part = base / STEP % parts;
+    u32* tick = parts == 1 ? ticket(a) : ws_ptr<u32>(*event_at(a, part), 0) + CTL_CTR;   // ctl is at offset 0
+    auto draw_ticket = [&]() { return nstatic + (atomicAdd(tick, 1u) * parts + part) * STEP; };
     const bool dyn = nstatic < total;             // tickets needed at all
     const bool drawer = WAVE ? lt == 0 : tid == 0;
     u32 round = 0;                                // round of the current module (>= nrounds: dynamic)
     u32 nv = total;                               // ticket of the next dynamic module (in flight)
     if (dyn && nrounds == 1) {
-        if (drawer) nv = atomicAdd(ticket(a), STEP) + nstatic;
+        if (drawer) nv = draw_ticket();
         if constexpr (!WAVE) {                    // every wave reads it at its first module's first stage
             if (tid == 0) s.tick = nv;
             lds_barrier();
@@ -1351,16 +1370,17 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     while (base < total) {
         u32 nbase = total, nv2 = total;
         Next N{};
+        N.E = E;
         bool have = false;
         Item In{0, 0, 0, 0, 0, false};
-        u32 NRC[K], NA[K];
+        u32 NRC[K];
         auto mid = [&](int stage) {
             if (stage == 0) {
                 const bool snext = round + 1 < nrounds;            // next module static
                 const bool draw = dyn && round + 2 >= nrounds;     // module after next dynamic
                 if (snext) nbase = base + per_round;
                 else if (dyn) nbase = WAVE ? wave_uniform(nv) : wave_uniform(s.tick);
-                if (draw && drawer && nbase < total) nv2 = atomicAdd(ticket(a), STEP) + nstatic;
+                if (draw && drawer && nbase < total) nv2 = draw_ticket();
                 have = nbase + ofs < total;
                 if (have) step_module(nbase + ofs, N);
             } else if (stage == 1) {
@@ -1371,13 +1391,13 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
                     if (tid == 0) s.tick = nv2;
                 if (have) {
                     In = step_item(N);
-                    if (In.ok) fetch_digis<G, K>(N.E, In, lt, NRC, NA);
+                    if (In.ok) fetch_digis<G, K>(*N.E, In, lt, NRC, A);
                 }
             }
         };
-        if (base + ofs < total && !I.ok && lt == 0) skip(E, I);
+        if (base + ofs < total && !I.ok && lt == 0) skip(*E, I);
         if (!WAVE || I.ok) {
-            cluster_regs<G, K, MPW == 1>(a, E, ev_layout(E.cap, a.n_modules), I, gp, lt, RC, A, mid);
+            cluster_regs<G, K, MPW == 1>(a, *E, ev_layout(E->cap, a.n_modules), I, gp, lt, RC, A, mid);
         } else {
             mid(0);
             mid(1);
@@ -1389,7 +1409,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
         nv = nv2;
         ++round;
 #pragma unroll
-        for (u32 q = 0; q < K; ++q) { RC[q] = NRC[q]; A[q] = NA[q]; }
+        for (u32 q = 0; q < K; ++q) RC[q] = NRC[q];
     }
 }
 
@@ -2100,6 +2120,7 @@ __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
             // compacted, the lists and error bits stay for it, the host learns why
             if (b + 1 == nblk && part == 0 && lane == 0) {
                 ctl[CTL_DEFERRED] = 1u;
+                ctl[CTL_CTR] = 0u;
                 u32* hs = (u32*)E.hstat;
                 st_sys(&hs[HS_ERR], ctl[CTL_ERR] | EB_DEFER);
                 st_sys(&hs[HS_NCL], 0u);
@@ -2122,6 +2143,7 @@ __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
             const u32 ncl = fits ? base + T : E.n;
             const u32 err = ctl[CTL_ERR];
             ctl[CTL_ERR] = 0u;
+            ctl[CTL_CTR] = 0u;
             st_ag(ctl + CTL_BIG, 0u);                      // the big kernels have run (other waves
             st_ag(ctl + CTL_SCR, 0u);                      // of the event may read them atomically)
             ctl[CTL_NCL] = ncl;
