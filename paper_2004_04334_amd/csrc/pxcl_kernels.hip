@@ -2144,6 +2144,8 @@ __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
             const u32 err = ctl[CTL_ERR];
             ctl[CTL_ERR] = 0u;
             ctl[CTL_CTR] = 0u;
+            // an empty event has no segmentation, which clears this for the next launch
+            if (!E.n) ctl[CTL_PRESENT + ((E.slot & 1u) ^ 1u)] = 0u;
             st_ag(ctl + CTL_BIG, 0u);                      // the big kernels have run (other waves
             st_ag(ctl + CTL_SCR, 0u);                      // of the event may read them atomically)
             ctl[CTL_NCL] = ncl;
