@@ -43,7 +43,7 @@ constexpr u32 C_WG = 256;                                   // compaction: a wav
 constexpr u32 K_SMALL = 8;                                  // digis per thread (small-module kernel)
 constexpr u32 B_WG = 1024, K_BIG = 16;                      // big-module kernel
 constexpr u32 BIG_RCAP = B_WG * K_BIG;                      // 16384: larger modules use scratch mode
-constexpr u32 S_WG = 1024;                                  // scratch-mode kernel
+constexpr u32 S_WG = 1024;                                  // its scratch mode
 
 // Per-event control words (u32) at the start of an event workspace.
 enum : u32 {
@@ -59,8 +59,9 @@ enum : u32 {
                       // first is one of the small kernel's tickets (zero between launches)
     CTL_WORDS = 64
 };
-// Launch counters: the small-module kernel's ticket (when it needs only one).
-enum : u32 { S_TICK = 0, N_CTR = 8 };
+// Launch counters: the small-module kernel's ticket (when it needs only one) and the
+// big-module kernel's.
+enum : u32 { S_TICK = 0, S_BIG = 1, N_CTR = 8 };
 // Host status block (pinned) written by the compaction kernel.
 enum : u32 { HS_EPOCH = 0, HS_ERR = 1, HS_NCL = 2, HS_WORDS = 16 };
 constexpr u32 HS_BYTES = HS_WORDS * 4;
@@ -77,7 +78,7 @@ constexpr u32 LF_NO_BIG = 1;     // the big-module kernel is not launched (size 
 constexpr u32 LF_SEG_WIDE = 2;   // segmentation in wide chunks
 constexpr u32 LF_FUSED = 4;      // one event, no segmentation kernel: the small kernel
                                  // finds every module's digis by search
-constexpr u32 LF_NO_SCRATCH = 8; // the scratch-mode kernel is not launched (size hint)
+constexpr u32 LF_NO_SCRATCH = 8; // no module for the scratch mode (size hint)
 constexpr u32 LF_GROUP = 16;     // some event is in any order: the grouping kernels run first
 constexpr u32 LF_NO_SEG = 32;    // no event is grouped by module: no segmentation kernel
 constexpr u32 LF_DEFER = 64;     // with LF_NO_BIG | LF_NO_SCRATCH: modules above the small

@@ -16,10 +16,9 @@
 //            to the big-module or the scratch-mode list.  Groups take modules by
 //            static rounds, then an atomic ticket, and prefetch the next module
 //            while working on the current one.
-//   big      one listed module per 512-thread workgroup, digis held in registers
-//            (up to 16,384 per module).
-//   scratch  one listed module above 16,384 digis per 1,024-thread workgroup, the
-//            digis re-read from memory in three passes.
+//   big      one listed module per 1,024-thread workgroup: up to 16,384 digis in
+//            register mode (digis held in registers), above that in scratch mode (the
+//            digis re-read from memory in three passes).
 //   compact  a wave per module: the offset of its clusters (the kept counts of the
 //            modules before it) and a copy of its staged records to their final
 //            position; a wave per event writes the status back to the host.
@@ -112,6 +111,10 @@ __device__ __forceinline__ const EventDesc* event_at(const LaunchArgs& a, u32 e)
 }
 __device__ __forceinline__ EventDesc get_event(const LaunchArgs& a, u32 e) { return *event_at(a, e); }
 __device__ __forceinline__ u32* ticket(const LaunchArgs& a) { return (u32*)(a.ctr + S_TICK); }
+__device__ __forceinline__ void reset_tickets(const LaunchArgs& a) {
+    st_ag(ticket(a), 0u);
+    st_ag((u32*)(a.ctr + S_BIG), 0u);
+}
 template <typename T>
 __device__ __forceinline__ T* ws_ptr(const EventDesc& E, size_t off) {
     return (T*)(T PXCL_G*)(E.ws + off);         // generic again, but known to be global
@@ -452,9 +455,9 @@ __global__ __launch_bounds__(G_WG) void k_group_count(LaunchArgs a) {
     const u32 tid = threadIdx.x, k = num_events(a), M = a.n_modules;
     const bool lds = M <= G_HMAX;                 // else ranks straight from the totals
     const u32 total = event_prefix<G_WG>(a, k, s_pref, s_wsum, CNT_ANY, G_CH, 0);
-    // the small kernel's ticket starts at zero (segmentation, which also resets it,
-    // is not launched when every event of the launch is in any order)
-    if (blockIdx.x == 0 && tid == 0) st_ag(ticket(a), 0u);
+    // the tickets start at zero (segmentation, which also resets them, is not launched
+    // when every event of the launch is in any order)
+    if (blockIdx.x == 0 && tid == 0) reset_tickets(a);
     for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
         const u32 e = find_slot(s_pref, k, t), c = t - s_pref[e];
         const EventDesc E = get_event(a, e);
@@ -632,10 +635,10 @@ __global__ __launch_bounds__(A_WG) void k_segment(LaunchArgs a) {
     const u32 tid = threadIdx.x;
     const u32 k = num_events(a);
     const u32 total = event_prefix<A_WG>(a, k, s_pref, s_wsum, CNT_SORTED, CH, 0);
-    // The small kernel's ticket starts at zero in every launch: the compaction kernel
-    // of a finished launch resets it, and this reset also covers a launch whose later
-    // kernels were never queued.
-    if (blockIdx.x == 0 && tid == 0) st_ag(ticket(a), 0u);
+    // The tickets start at zero in every launch: the compaction kernel of a finished
+    // launch resets them, and this reset also covers a launch whose later kernels were
+    // never queued.
+    if (blockIdx.x == 0 && tid == 0) reset_tickets(a);
 
     for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
         if (tid == 0) s_err = 0;
@@ -1414,7 +1417,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
 }
 
 // ---------------------------------------------------------------------------
-// big: one module per 512-thread workgroup
+// big: one module per 1,024-thread workgroup
 // ---------------------------------------------------------------------------
 // Register mode: up to BIG_RCAP digis, K per thread of a 1,024-thread workgroup.  At such
 // occupancies most work is per digi, and one workgroup has the compute unit to itself (the
@@ -2025,40 +2028,41 @@ __device__ __forceinline__ Item big_item(const LaunchArgs& a, const u32* s_pref,
     return I;
 }
 
-// big, register mode: the modules of the big-module list (above the small kernel's
-// capacity, up to BIG_RCAP digis)
+// Both modes in one launch: the modules of the scratch-mode list (above BIG_RCAP digis), which
+// take longest, then those of the big-module list.  A workgroup's first module is given by its
+// index, the others by ticket, so a workgroup busy with a scratch-mode module takes no more
+// than that while the rest share the others.  16 events with a serpentine and 16-20 modules
+// of 2,049 to 13,312 digis each: 92 us, where a launch per mode took 57 + 82 (118 us with
+// tickets drawn when a module starts: those of the scratch-mode workgroups waited with them);
+// launched for no module at all it costs one launch instead of two.
+static_assert(B_WG == S_WG, "the modes share the workgroup");
 __global__ __launch_bounds__(B_WG) void k_big(LaunchArgs a) {
-    __shared__ DenseSmem<B_WG, K_BIG> s;
-    __shared__ u32 s_pref[MAXB + 1];
+    __shared__ union {
+        DenseSmem<B_WG, K_BIG> d;
+        BigScratchSmem<S_WG> x;
+    } s;                                      // both start with the bitmap, clear between modules
+    __shared__ u32 s_pref[MAXB + 1], s_xpref[MAXB + 1];
     __shared__ u32 s_wsum[B_WG / 64];
+    __shared__ u32 s_tick;
     const u32 tid = threadIdx.x;
-    for (u32 w = tid; w < BM_WORDS; w += B_WG) s.bm[w] = 0u;
+    for (u32 w = tid; w < BM_WORDS; w += B_WG) s.d.bm[w] = 0u;
     const u32 k = num_events(a);
-    const u32 total = event_prefix<B_WG>(a, k, s_pref, s_wsum, CTL_BIG, 1, 0);
-    for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
-        const Item I = big_item(a, s_pref, k, t, false);
-        if (!I.ok) continue;
-        const EventDesc E = get_event(a, I.e);
-        cluster_dense<B_WG, K_BIG>(a, E, ev_layout(E.cap, a.n_modules), I, s);
-    }
-}
-
-// big, scratch mode: the modules of the scratch-mode list (above BIG_RCAP digis), in
-// workgroups of S_WG threads (more waves for the column-ordered unions, a chain of
-// steps per wave)
-__global__ __launch_bounds__(S_WG) void k_scratch(LaunchArgs a) {
-    __shared__ BigScratchSmem<S_WG> s;
-    __shared__ u32 s_pref[MAXB + 1];
-    __shared__ u32 s_wsum[S_WG / 64];
-    const u32 tid = threadIdx.x;
-    for (u32 w = tid; w < BM_WORDS; w += S_WG) s.bm[w] = 0u;
-    const u32 k = num_events(a);
-    const u32 total = event_prefix<S_WG>(a, k, s_pref, s_wsum, CTL_SCR, 1, 0);
-    for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
-        const Item I = big_item(a, s_pref, k, t, true);
-        if (!I.ok) continue;
-        const EventDesc E = get_event(a, I.e);
-        cluster_scratch<S_WG>(a, E, ev_layout(E.cap, a.n_modules), I, s);
+    const u32 xtotal = event_prefix<B_WG>(a, k, s_xpref, s_wsum, CTL_SCR, 1, 0);
+    const u32 total = xtotal + event_prefix<B_WG>(a, k, s_pref, s_wsum, CTL_BIG, 1, 0);
+    for (u32 t = blockIdx.x; t < total;) {
+        const bool scr = t < xtotal;
+        const Item I = wave_uniform(big_item(a, scr ? s_xpref : s_pref, k, scr ? t : t - xtotal, scr));
+        if (I.ok) {                           // the same for the whole workgroup
+            const EventDesc E = get_event(a, I.e);
+            const EvLayout L = ev_layout(E.cap, a.n_modules);
+            if (scr) cluster_scratch<S_WG>(a, E, L, I, s.x);
+            else cluster_dense<B_WG, K_BIG>(a, E, L, I, s.d);
+        }
+        if (total <= gridDim.x) break;
+        if (tid == 0) s_tick = atomicAdd((u32*)(a.ctr + S_BIG), 1u) + gridDim.x;   // not before: it would wait with us
+        lds_barrier();
+        t = wave_uniform(s_tick);
+        lds_barrier();                        // read by every wave before the next draw is stored
     }
 }
 
@@ -2105,7 +2109,7 @@ __device__ __forceinline__ u32 kept_before(const u32* kept, u32 end, u32 lane) {
 __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
     const u32 tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
     const u32 k = num_events(a), M = a.n_modules, nblk = compact_blocks(M);
-    if (blockIdx.x == 0 && tid == 0) st_ag(ticket(a), 0u);   // the small kernel has finished
+    if (blockIdx.x == 0 && tid == 0) reset_tickets(a);            // the kernels that draw them have finished
     const u32 sp = compact_split(gridDim.x * C_WAVES, k * nblk);
     const u32 total = k * nblk * sp;
     for (u32 u = wave_uniform(xcd_order(blockIdx.x, gridDim.x) * C_WAVES + wv); u < total; u += gridDim.x * C_WAVES) {
@@ -2328,7 +2332,6 @@ int occupancy_cluster(u32 wg, u32 mpw) {
     return f ? occ(reinterpret_cast<const void*>(f), int(wg)) : 0;
 }
 int occupancy_big() { return occ(reinterpret_cast<const void*>(k_big), B_WG); }
-int occupancy_scratch() { return occ(reinterpret_cast<const void*>(k_scratch), S_WG); }
 int occupancy_compact() { return occ(reinterpret_cast<const void*>(k_compact), C_WG); }
 
 int occupancy_group() {
@@ -2359,12 +2362,11 @@ hipError_t launch_small(u32 wg, u32 mpw, const LaunchArgs& a, u32 grid, hipStrea
     hipLaunchKernelGGL(f, dim3(grid), dim3(wg), 0, s, a);
     return hipGetLastError();
 }
-// The two big-module kernels (register mode, then scratch mode unless LF_NO_SCRATCH).
+// The big-module kernel: workgroups for `grid` register-mode and `grid_scratch` scratch-mode
+// modules (none of those with LF_NO_SCRATCH); with fewer, modules wait for a ticket.
 hipError_t launch_big(const LaunchArgs& a, u32 grid, u32 grid_scratch, hipStream_t s) {
-    hipLaunchKernelGGL(k_big, dim3(grid), dim3(B_WG), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || (a.flags & LF_NO_SCRATCH)) return e;
-    hipLaunchKernelGGL(k_scratch, dim3(grid_scratch), dim3(S_WG), 0, s, a);
+    const u32 g = std::max(grid, (a.flags & LF_NO_SCRATCH) ? 1u : grid_scratch);
+    hipLaunchKernelGGL(k_big, dim3(g), dim3(B_WG), 0, s, a);
     return hipGetLastError();
 }
 u32 compact_waves_per_block(u32 waves, u32 blocks) { return compact_split(waves, blocks); }

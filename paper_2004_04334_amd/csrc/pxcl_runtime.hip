@@ -39,7 +39,6 @@ int occupancy_compact();
 hipError_t launch_segment(const LaunchArgs& a, u32 grid, hipStream_t s);
 hipError_t launch_small(u32 wg, u32 mpw, const LaunchArgs& a, u32 grid, hipStream_t s);
 hipError_t launch_big(const LaunchArgs& a, u32 grid, u32 grid_scratch, hipStream_t s);
-int occupancy_scratch();
 hipError_t launch_compact(const LaunchArgs& a, u32 grid, hipStream_t s);
 u32 compact_waves_per_block(u32 waves, u32 blocks);
 int occupancy_hits();
@@ -107,7 +106,7 @@ struct pxcl_ctx {
     u32 n_cu = 0;
     std::string arch;
     std::atomic<u32> wg{256}, mpw{1};
-    int occ_a = 1, occ_l = 1, occ_c = 1, occ_h = 1, occ_x = 1, occ_g = 1;
+    int occ_a = 1, occ_l = 1, occ_c = 1, occ_h = 1, occ_g = 1;
     int occ_s[4][5] = {};               // small kernel per shape [log2(wg) - 6][mpw], queried once
     std::atomic<int> bound{0};
     std::atomic<int> timing{0};
@@ -231,10 +230,9 @@ Grids grids_for(const pxcl_ctx* ctx, u32 wg, u32 mpw, u64 digis, u64 present, u3
     const u64 fb = ncu * (u64)ctx->occ_l;
     const u64 fs = ncu * (u64)ctx->occ_s[31 - __builtin_clz(wg) - 6][mpw];
     const u64 fc = ncu * (u64)ctx->occ_c;
-    // modules above BIG_RCAP digis are rare outliers (one per stress event): the scratch
-    // kernel's workgroups, each holding a whole compute unit's LDS, are capped at a
-    // quarter of the chip, the rest loop
-    const u64 fx = std::min<u64>(ncu * (u64)ctx->occ_x, std::max<u64>(ncu / 4, 1));
+    // workgroups for modules above BIG_RCAP digis, rare outliers (one per stress event): at
+    // most a quarter of the chip; they count only in launches with next to no others
+    const u64 fx = std::min<u64>(fb, std::max<u64>(ncu / 4, 1));
     const u64 fg = ncu * (u64)ctx->occ_g;
     if (full) {
         g.a = u32(fa); g.b = u32(fb); g.s = u32(fs); g.c = u32(fc); g.x = u32(fx);
@@ -552,7 +550,6 @@ extern "C" int pxcl_ctx_create(const pxcl_config* cfg, int device, pxcl_ctx** ou
         for (u32 m = 1; m <= 4; m *= 2)
             if (cluster_config_valid(w, m)) c->occ_s[31 - __builtin_clz(w) - 6][m] = occupancy_cluster(w, m);
     c->occ_l = occupancy_big();
-    c->occ_x = occupancy_scratch();
     c->occ_c = occupancy_compact();
     c->occ_h = occupancy_hits();
     c->occ_g = occupancy_group();
