@@ -146,6 +146,17 @@ struct LaunchArgs {
     EventDesc single;
 };
 
+// Arrays copied between pinned host memory and the device by one kernel: 8-byte aligned at
+// both ends, whole 8-byte words and then a tail of 16-bit values.
+constexpr u32 MAX_COPIES = 6;
+struct CopyArgs {
+    const u64 PXCL_G* src[MAX_COPIES];
+    u64 PXCL_G* dst[MAX_COPIES];
+    u32 first[MAX_COPIES + 1];   // words of the arrays before each one; the last: of all
+    u32 tail[MAX_COPIES];        // 16-bit values after an array's words (at most 3)
+    u32 n;
+};
+
 PXCL_HD constexpr size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Byte offsets of the arrays of an event workspace with capacity N digis and M
