@@ -90,9 +90,9 @@ PXCL_HD constexpr u32 seg_chunk(u32 flags) { return A_WG * ((flags & LF_SEG_WIDE
 
 // Event flags (EventDesc::flags).
 constexpr u32 EF_UNSORTED = 1;   // the digis are in any order: the grouping kernels read them
-                                 // from r_*, write a copy grouped by module to the workspace
-                                 // (module..adc point there) and each grouped digi's input
-                                 // position (perm), where its per-digi output goes
+                                 // from r_* and write a copy grouped by module to the workspace
+                                 // (grp: one word per digi, its input position in it), which
+                                 // the other kernels read instead of module..adc
 constexpr u32 EF_HITS = 2;       // hits fused into the clustering: every kept digi adds
                                  // adc*col and adc*row to its cluster's staging sums (hsum),
                                  // the compaction writes x and y beside each record and
@@ -102,7 +102,7 @@ constexpr u32 EF_HITS = 2;       // hits fused into the clustering: every kept d
 
 // One event as the kernels see it (144 bytes).
 struct EventDesc {
-    const u16 PXCL_G* module;   // digis grouped by module (the input, or the workspace's grouped copy)
+    const u16 PXCL_G* module;   // digis grouped by module
     const u16 PXCL_G* row;
     const u16 PXCL_G* col;
     const u16 PXCL_G* adc;
@@ -172,8 +172,8 @@ struct EvLayout {
     size_t present;                          // module ids of the modules present (any order)
     size_t off;                              // per module: its first cluster in the outputs
     size_t hit_x, hit_y;                     // hits (per kept cluster), when asked for
-    size_t perm;                             // digis in any order: input index of each grouped digi
-    size_t grp;                              // digis in any order: the grouped copy (4 x u16[N])
+    size_t perm;                             // (4N bytes, not used)
+    size_t grp;                              // digis in any order: the grouped copy (u64[N])
     size_t gcnt;                             // digis in any order: per module, digis counted (zero between launches)
     size_t hsum;                             // fused hits: per staged record, sum(adc*col), sum(adc*row) (u64)
     size_t total;

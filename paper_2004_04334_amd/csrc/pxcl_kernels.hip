@@ -119,12 +119,34 @@ template <typename T>
 __device__ __forceinline__ T* ws_ptr(const EventDesc& E, size_t off) {
     return (T*)(T PXCL_G*)(E.ws + off);         // generic again, but known to be global
 }
-// Digis in any order: the input position of grouped digi p is perm[p]; per-digi
-// outputs go there.  nullptr when the digis came grouped (position p itself).
-__device__ __forceinline__ const u32* perm_of(const EventDesc& E, const EvLayout& L) {
-    return (E.flags & EF_UNSORTED) ? ws_ptr<const u32>(E, L.perm) : nullptr;
+// The digis of a module.  Given grouped by module they are the input's arrays; of an event in
+// any order each is one word of the workspace's grouped copy: adc in bits 0-15, row in 16-23,
+// column in 24-32 (255 and 511 for a pixel outside the module) and the input position, where
+// its per-digi output goes, above.
+__device__ __forceinline__ u64 pack_digi(u32 row, u32 col, u32 adc, u32 pos) {
+    const u32 rc = row < ROWS && col < COLS ? row | (col << 8) : 0x1FFFFu;
+    return u64(adc) | (u64(rc) << 16) | (u64(pos) << 33);
 }
-__device__ __forceinline__ u32 out_pos(const u32* perm, u32 p) { return perm ? perm[p] : p; }
+struct ModuleDigis {
+    const u16 *row, *col, *adc;
+    const u64* rec;              // nullptr: the arrays
+    u32 st;
+    static __device__ __forceinline__ u32 rc_of(u64 v) { return (u32(v >> 16) & 0xFFu) | ((u32(v >> 24) & 0x1FFu) << 16); }
+    static __device__ __forceinline__ u32 pos_of(u64 v) { return u32(v >> 33); }
+    // row | column << 16, adc and output position of the module's j-th digi
+    __device__ __forceinline__ u32 rc(u32 j) const { return rec ? rc_of(rec[j]) : u32(row[j]) | (u32(col[j]) << 16); }
+    __device__ __forceinline__ u32 adc_at(u32 j) const { return rec ? u32(rec[j]) & 0xFFFFu : u32(adc[j]); }
+    __device__ __forceinline__ u32 pos(u32 j) const { return rec ? pos_of(rec[j]) : st + j; }
+};
+__device__ __forceinline__ ModuleDigis module_digis(const EventDesc& E, const EvLayout& L, u32 st) {
+    ModuleDigis D;
+    D.row = (const u16*)E.row + st;
+    D.col = (const u16*)E.col + st;
+    D.adc = (const u16*)E.adc + st;
+    D.rec = (E.flags & EF_UNSORTED) ? ws_ptr<const u64>(E, L.grp) + st : nullptr;
+    D.st = st;
+    return D;
+}
 
 // Inclusive scan across the 64 lanes of a wave.
 __device__ __forceinline__ u32 wave_incl_scan(u32 v) {
@@ -417,7 +439,7 @@ __device__ __forceinline__ void word_links(const u32* bm, const u64* col, u32 c,
 // ---------------------------------------------------------------------------
 // group (digis in any order): a counting sort by module ahead of the clustering,
 // which then reads a grouped copy in the event workspace and writes every per-digi
-// output at the digi's input position (perm).  Three kernels:
+// output at the digi's input position.  Three kernels:
 //   count    per chunk of G_CH digis an LDS histogram over the modules gives each
 //            digi its rank among the chunk's digis of its module; one device atomic
 //            per (chunk, module present in it) adds the chunk's count to the module's
@@ -429,23 +451,15 @@ __device__ __forceinline__ void word_links(const u32* bm, const u64* col, u32 c,
 //            each module its first grouped position; module-table entries tagged with
 //            the launch, the present-module list in ascending module order, kept
 //            counts and totals cleared -- the segmentation kernel's outputs.
-//   scatter  every digi goes to first[module] + rank of the grouped copy, and its
-//            input position to perm.
+//   scatter  every digi goes to first[module] + rank of the grouped copy.  What bounds it is
+//            the number of scattered stores (a wave's 64 digis go to dozens of modules), so a
+//            digi is one word: 16 events of 64,000 digis 31.7 -> 15.5 us (row, column, adc,
+//            module and input position stored one by one before).
 // A digi's place within its module is not fixed (chunks take their bases in any
 // order); the clustering does not depend on it.
 // ---------------------------------------------------------------------------
 constexpr u32 G_WG = 256, G_PER = 16, G_CH = G_WG * G_PER, G_HMAX = 4096, G_TPM = 8;
 constexpr u32 G_SPER = 4, G_SCH = G_WG * G_SPER;   // scatter: smaller chunks, more workgroups
-
-struct GroupArrays {
-    u16 *m, *r, *c, *a;
-    u32* perm;
-};
-__device__ __forceinline__ GroupArrays group_arrays(const EventDesc& E, const EvLayout& L) {
-    u16* g = ws_ptr<u16>(E, L.grp);
-    const size_t N = E.cap;
-    return GroupArrays{g, g + N, g + 2 * N, g + 3 * N, ws_ptr<u32>(E, L.perm)};
-}
 
 __global__ __launch_bounds__(G_WG) void k_group_count(LaunchArgs a) {
     __shared__ u32 hist[G_HMAX];
@@ -582,7 +596,7 @@ __global__ __launch_bounds__(G_WG) void k_group_scatter(LaunchArgs a) {
         const EvLayout L = ev_layout(E.cap, M);
         const ModRange* mt = ws_ptr<const ModRange>(E, L.mtab);
         const u32* rank = (const u32*)E.o_digi;
-        const GroupArrays G = group_arrays(E, L);
+        u64* rec = ws_ptr<u64>(E, L.grp);
         // every load first (module ids, then table entries, ranks and the digis), then
         // the stores: stores to the grouped copy could alias the input for the compiler,
         // which would otherwise keep each digi's loads behind the previous digi's stores
@@ -609,11 +623,7 @@ __global__ __launch_bounds__(G_WG) void k_group_scatter(LaunchArgs a) {
         for (u32 q = 0; q < G_SPER; ++q) {
             const u32 p = pos[q];
             if (p == NOPIX) continue;
-            G.m[p] = u16(mm[q]);
-            G.r[p] = u16(rr[q]);
-            G.c[p] = u16(cc[q]);
-            G.a[p] = u16(aa[q]);
-            G.perm[p] = i0 + q * G_WG;
+            rec[p] = pack_digi(rr[q], cc[q], aa[q], i0 + q * G_WG);
         }
     }
 }
@@ -783,18 +793,30 @@ __device__ __forceinline__ EventDesc wave_uniform(const EventDesc& E) {
 // Issue the loads of the module's digis j = lt + q*G < n: row and column packed in
 // one register (row | col << 16, half-word loads into each half), adc in another; the
 // values are only used when the module is clustered, so the loads stay in flight
-// meanwhile.
+// meanwhile (those of an event in any order are unpacked here, and waited for).
 template <u32 G, u32 K>
-__device__ __forceinline__ void fetch_digis(const EventDesc& E, const Item& I, u32 lt, u32* RC, u32* A) {
-    const u16 *row = (const u16*)E.row + I.st, *col = (const u16*)E.col + I.st, *adc = (const u16*)E.adc + I.st;
+__device__ __forceinline__ void fetch_digis(const ModuleDigis& D, u32 n, u32 lt, u32* RC, u32* A) {
+    if (D.rec) {
+        u64 v[K];
+#pragma unroll
+        for (u32 q = 0; q < K; ++q)
+            if (q * G < n && lt + q * G < n) v[q] = D.rec[lt + q * G];
+#pragma unroll
+        for (u32 q = 0; q < K; ++q) {
+            const bool in = q * G < n && lt + q * G < n;
+            RC[q] = in ? ModuleDigis::rc_of(v[q]) : NOPIX;
+            A[q] = in ? u32(v[q]) & 0xFFFFu : 0u;
+        }
+        return;
+    }
 #pragma unroll
     for (u32 q = 0; q < K; ++q) {
         const u32 j = lt + q * G;
         RC[q] = NOPIX;
         A[q] = 0u;
-        if (q * G < I.n && j < I.n) {
-            RC[q] = u32(row[j]) | (u32(col[j]) << 16);
-            A[q] = adc[j];
+        if (q * G < n && j < n) {
+            RC[q] = u32(D.row[j]) | (u32(D.col[j]) << 16);
+            A[q] = D.adc[j];
         }
     }
 }
@@ -1015,8 +1037,8 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
         int32_t* tid_ = ws_ptr<int32_t>(E, L.tid) + I.st;
         int32_t* tch = ws_ptr<int32_t>(E, L.tcharge) + I.st;
         int32_t* tsz = ws_ptr<int32_t>(E, L.tsize) + I.st;
-        const u32* perm = perm_of(E, L);
-        int32_t* od = (int32_t*)E.o_digi + (perm ? 0u : I.st);
+        const ModuleDigis D = module_digis(E, L, I.st);
+        int32_t* od = (int32_t*)E.o_digi + (D.rec ? 0u : I.st);
         const u32 idbase = I.mod * PIX;
 #pragma unroll
         for (u32 q = 0; q < K; ++q) {
@@ -1037,13 +1059,13 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
                         }
                         if (hits) {
                             const u32 p = position(X[q]);
-                            const u64 w = E.adc[I.st + j];             // A holds the next module's
+                            const u64 w = D.adc_at(j);                 // A holds the next module's
                             atomicAdd(&hs[2 * p], w * c);
                             atomicAdd(&hs[2 * p + 1], w * row);
                         }
                     }
                 }
-                od[perm ? perm[I.st + j] : j] = id;
+                od[D.rec ? ModuleDigis::pos_of(D.rec[j]) : j] = id;
             }
         }
         if (err) atomicOr(ws_ptr<u32>(E, L.ctl) + CTL_ERR, err);
@@ -1348,7 +1370,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
         step_range(N);
         I = step_item(N);
         E = N.E;
-        if (I.ok) fetch_digis<G, K>(*E, I, lt, RC, A);
+        if (I.ok) fetch_digis<G, K>(module_digis(*E, ev_layout(E->cap, a.n_modules), I.st), I.n, lt, RC, A);
     }
     if (fused) id_check_finish<WG>(a, get_event(a, 0), idc);
     // (units of a launch: at most MAXB * PXCL_MAX_MODULES, so three times that fits 32 bits)
@@ -1394,7 +1416,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
                     if (tid == 0) s.tick = nv2;
                 if (have) {
                     In = step_item(N);
-                    if (In.ok) fetch_digis<G, K>(*N.E, In, lt, NRC, A);
+                    if (In.ok) fetch_digis<G, K>(module_digis(*N.E, ev_layout(N.E->cap, a.n_modules), In.st), In.n, lt, NRC, A);
                 }
             }
         };
@@ -1445,15 +1467,10 @@ __device__ __forceinline__ void cluster_dense(const LaunchArgs& a, const EventDe
     static_assert(G * K <= 16384, "sizes of up to 15 bits, run numbers of up to 16");
     const u32 tid = threadIdx.x, n = I.n, st = I.st;
     const u32 nq = min((n + G - 1) / G, K);
-    const u16 *prow = (const u16*)E.row + st, *pcol = (const u16*)E.col + st, *padc = (const u16*)E.adc + st;
+    const ModuleDigis D = module_digis(E, L, st);
     const bool hits = (E.flags & EF_HITS) != 0;
     u32 RC[K], A[K], X[K], valid = 0, err = 0, dup = 0;
-#pragma unroll
-    for (u32 q = 0; q < K; ++q) {                              // every slot loads a digi of the module
-        const u32 j = tid + q * G < n ? tid + q * G : 0u;
-        RC[q] = u32(prow[j]) | (u32(pcol[j]) << 16);
-        A[q] = padc[j];
-    }
+    fetch_digis<G, K>(D, n, tid, RC, A);
     if (tid < KBW) s.kb[tid] = 0u;
 #pragma unroll
     for (u32 q = 0; q < K; ++q)
@@ -1556,7 +1573,6 @@ __device__ __forceinline__ void cluster_dense(const LaunchArgs& a, const EventDe
         });
     }
     int32_t* od = (int32_t*)E.o_digi;
-    const u32* perm = perm_of(E, L);
     u32 keep = 0;
 #pragma unroll
     for (u32 q = 0; q < K; ++q) {
@@ -1570,7 +1586,7 @@ __device__ __forceinline__ void cluster_dense(const LaunchArgs& a, const EventDe
                     keep |= 1u << q;
                 }
             }
-            od[out_pos(perm, st + j)] = id;
+            od[D.pos(j)] = id;
         }
     }
     for (u32 w = tid; w < WORDS; w += G) s.bm[BM_FRONT + w] = 0u;
@@ -1661,11 +1677,10 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     u32* cch = (u32*)E.o_charge + st;   // per cluster: charge
     u32* csz = (u32*)E.o_size + st;     // per cluster: size
     int32_t* od = (int32_t*)E.o_digi;
-    const u32* perm = perm_of(E, L);
+    const ModuleDigis D = module_digis(E, L, st);
     const bool hits = (E.flags & EF_HITS) != 0;
     u64* hs = ws_ptr<u64>(E, L.hsum);
     u32 err = 0;
-    const u16 *prow = (const u16*)E.row + st, *pcol = (const u16*)E.col + st, *padc = (const u16*)E.adc + st;
     const u32 wv = tid >> 6, lane = tid & 63u;
     // A step: this thread's digis base + 4 * (u * BW + tid) + 0..3, u < UNR; quads past the
     // module's end are passed over by the whole workgroup.
@@ -1678,6 +1693,25 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
         for (u32 i = 0; i < 4; ++i)
             if (first + i < n) v |= u64(p[first + i]) << (16 * i);
         return v;
+    };
+    auto load = [&](u32 base, u32 u, u64& r, u64& c, u64* w) {     // rows, columns and, with w, adcs
+        if (!D.rec) {
+            r = quad(D.row, base, u);
+            c = quad(D.col, base, u);
+            if (w) *w = quad(D.adc, base, u);
+            return;
+        }
+        const u32 first = first_of(base, u);
+        u64 v[4];
+        for (u32 i = 0; i < 4; ++i) v[i] = first + i < n ? D.rec[first + i] : 0ull;
+        r = c = 0ull;
+        if (w) *w = 0ull;
+        for (u32 i = 0; i < 4; ++i) {
+            const u32 rc = ModuleDigis::rc_of(v[i]);
+            r |= u64(rc & 0xFFFFu) << (16 * i);
+            c |= u64(rc >> 16) << (16 * i);
+            if (w) *w |= (v[i] & 0xFFFFu) << (16 * i);
+        }
     };
     // the wave's quads hold four pixels each (else each digi is looked at by itself)
     auto whole = [&](u32 base, u32 u, u64 r, u64 c) {
@@ -1693,10 +1727,7 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
         u64 r[UNR], c[UNR];
 #pragma unroll
         for (u32 u = 0; u < UNR; ++u)
-            if (some(base, u)) {
-                r[u] = quad(prow, base, u);
-                c[u] = quad(pcol, base, u);
-            }
+            if (some(base, u)) load(base, u, r[u], c[u], nullptr);
         u32 dup = 0;
 #pragma unroll
         for (u32 u = 0; u < UNR; ++u) {
@@ -1833,7 +1864,7 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     lds_barrier();
     // Digi outputs at their own positions, and every cluster's sums in LDS: the usual case,
     // taken by the whole workgroup.
-    const bool plain = !perm && ncl <= LCAP;
+    const bool plain = !D.rec && ncl <= LCAP;
     auto cluster_at = [&](u32 row, u32 col) {
         return u32(cl[run_number(s.col[col + 1], row >> 5, s.bm[word_of(row, col)], row)]);
     };
@@ -1846,11 +1877,7 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
         u64 r[UNR], c[UNR], w[UNR];
 #pragma unroll
         for (u32 u = 0; u < UNR; ++u)
-            if (some(base, u)) {
-                r[u] = quad(prow, base, u);
-                c[u] = quad(pcol, base, u);
-                w[u] = quad(padc, base, u);
-            }
+            if (some(base, u)) load(base, u, r[u], c[u], &w[u]);
 #pragma unroll
         for (u32 u = 0; u < UNR; ++u) {
             if (!some(base, u)) continue;
@@ -1884,7 +1911,7 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
                 const u32 row = part(r[u], i), col = part(c[u], i), x = part(w[u], i);
                 const bool v = pixel(j + i, row, col);
                 const u32 k = v ? cluster_at(row, col) : 0u;
-                if (j + i < n) od[out_pos(perm, st + j + i)] = v ? int32_t(k) : -1;
+                if (j + i < n) od[D.pos(j + i)] = v ? int32_t(k) : -1;
                 wave_add<u64>(acc, k, (1ull << 44) | u64(x), v && k < LCAP);
                 wave_add<u32>(cch, k, x, v && k >= LCAP);
                 wave_add<u32>(csz, k, 1u, v && k >= LCAP);
@@ -1958,13 +1985,12 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
         // records' device sums take them whole), those of clusters beyond them by device
         // atomics.  One device atomic per digi took 1.25 ms for a 33,423-pixel serpentine.
         for (u32 axis = 0; axis < 2; ++axis) {
-            const u16* pc = axis ? prow : pcol;
             for (u32 c = tid; c < min(ncl, LCAP); c += BW) acc[c] = 0ull;
             lds_barrier();
             for (u32 j0 = 0; j0 < n; j0 += BW) {
                 const u32 j = j0 + tid;
-                const int32_t k = j < n ? od[out_pos(perm, st + j)] : -1;
-                const u64 x = k >= 0 ? u64(padc[j]) * pc[j] : 0ull;
+                const int32_t k = j < n ? od[D.pos(j)] : -1;
+                const u64 x = k >= 0 ? u64(D.adc_at(j)) * (axis ? D.rc(j) & 0xFFFFu : D.rc(j) >> 16) : 0ull;
                 const u32 c = k >= 0 ? u32(k) : 0u;
                 const bool kept = k >= 0 && ((s.rootb[c >> 5] >> (c & 31u)) & 1u);
                 wave_add<u64>(acc, c, x, kept && c < LCAP);
@@ -1994,7 +2020,7 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
 #pragma unroll 1
             for (u32 i = 0; i < 4; ++i) {
                 if (j + i >= n) continue;
-                const u32 q = out_pos(perm, st + j + i);
+                const u32 q = D.pos(j + i);
                 const int32_t k = od[q];
                 if (k >= 0) od[q] = int32_t(u32(k) < LCAP ? u32(acc[k]) : ld_ag(&cid[k]));
             }
@@ -2253,7 +2279,7 @@ __global__ __launch_bounds__(H_WG) void k_hits(LaunchArgs a) {
         const int32_t* ids = (const int32_t*)E.o_id + off;
         const int32_t* chg = (const int32_t*)E.o_charge + off;
         const int32_t* dcl = (const int32_t*)E.o_digi;
-        const u32* perm = perm_of(E, L);
+        const ModuleDigis D = module_digis(E, L, st);
         float* hx = ws_ptr<float>(E, L.hit_x) + off;
         float* hy = ws_ptr<float>(E, L.hit_y) + off;
         for (u32 c0 = 0; c0 < cnt; c0 += H_CAP) {
@@ -2266,7 +2292,7 @@ __global__ __launch_bounds__(H_WG) void k_hits(LaunchArgs a) {
             lds_barrier();
             const int32_t lo = s_id[0], hi = s_id[len - 1];
             for (u32 j = tid; j < nd; j += H_WG) {
-                const int32_t id = dcl[out_pos(perm, st + j)];
+                const int32_t id = dcl[D.pos(j)];
                 if (id < lo || id > hi) continue;          // cut (-1) or held by another chunk
                 u32 l = 0, h = len;
                 while (h - l > 1) {
@@ -2274,9 +2300,10 @@ __global__ __launch_bounds__(H_WG) void k_hits(LaunchArgs a) {
                     if (s_id[m] <= id) l = m; else h = m;
                 }
                 if (s_id[l] != id) continue;
-                const u64 w = E.adc[st + j];
-                atomicAdd(&s_sx[l], w * E.col[st + j]);
-                atomicAdd(&s_sy[l], w * E.row[st + j]);
+                const u32 rc = D.rc(j);
+                const u64 w = D.adc_at(j);
+                atomicAdd(&s_sx[l], w * (rc >> 16));
+                atomicAdd(&s_sy[l], w * (rc & 0xFFFFu));
             }
             lds_barrier();
             for (u32 c = tid; c < len; c += H_WG) {

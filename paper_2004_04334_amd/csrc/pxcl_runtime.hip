@@ -361,15 +361,13 @@ hipError_t make_desc(pxcl_event* ev, const pxcl_digis* in, hipStream_t s, EventD
     d->cap = ev->cap;
     d->epoch = ev->epoch;
     d->slot = ev->slot;
-    // digis in any order: the kernels read them through r_* and cluster the grouped
-    // copy the grouping kernels write to the workspace
+    // digis in any order: the grouping kernels read them through r_*, the others cluster the
+    // grouped copy that those write to the workspace
     const bool any = (in->flags & PXCL_DIGIS_ANY_ORDER) != 0;
     if (in->flags & PXCL_DIGIS_HITS) d->flags |= EF_HITS;
     const u16** dst[4] = {&d->module, &d->row, &d->col, &d->adc};
     if (any) {
         d->flags |= EF_UNSORTED;
-        u16* g = reinterpret_cast<u16*>(ev->ws + L.grp);
-        for (int i = 0; i < 4; ++i) *dst[i] = g + size_t(i) * ev->cap;
         dst[0] = &d->r_module; dst[1] = &d->r_row; dst[2] = &d->r_col; dst[3] = &d->r_adc;
     }
     if (in->where == PXCL_WHERE_DEVICE) {
