@@ -234,16 +234,20 @@ class Digis:
         return WHERE_DEVICE if self.module.is_cuda else WHERE_HOST
 
     def struct(self) -> _Digis:
-        ts = (self.module, self.row, self.col, self.adc)
-        for t in ts:
-            if t.dtype != torch.uint16 or not t.is_contiguous() or t.numel() != self.n:
+        # on the path of every acquire: each tensor is asked once
+        m, r, c, a = self.module, self.row, self.col, self.adc
+        n, cuda, u16 = m.numel(), m.is_cuda, torch.uint16
+        for t in (m, r, c, a):
+            if t.dtype != u16 or not t.is_contiguous() or t.numel() != n:
                 raise ValueError("digis must be contiguous uint16 tensors of equal length")
-            if t.is_cuda != self.module.is_cuda or (not t.is_cuda and not t.is_pinned()):
+            if t.is_cuda != cuda or (not cuda and not t.is_pinned()):
                 raise ValueError("digis must all be on the device or all in pinned host memory")
-        return _Digis(*(t.data_ptr() if self.n else None for t in ts), self.n, self.where,
-                      int(self.max_module_digis),
-                      (DIGIS_ANY_ORDER if self.any_order else 0) | (DIGIS_HITS if self.hits else 0) |
-                      (DIGIS_DEFER_BIG if self.defer_big else 0))
+        flags = ((DIGIS_ANY_ORDER if self.any_order else 0) | (DIGIS_HITS if self.hits else 0) |
+                 (DIGIS_DEFER_BIG if self.defer_big else 0))
+        where, most = WHERE_DEVICE if cuda else WHERE_HOST, int(self.max_module_digis)
+        if not n:
+            return _Digis(None, None, None, None, 0, where, most, flags)
+        return _Digis(m.data_ptr(), r.data_ptr(), c.data_ptr(), a.data_ptr(), n, where, most, flags)
 
     @staticmethod
     def from_numpy(ev, device: str = "cuda", hint: bool = False, any_order: bool = False,
@@ -333,6 +337,9 @@ class Event:
         self.ws = torch.empty(nb, dtype=torch.uint8, device=f"cuda:{ctx.device}")
         pb = int(lib().pxcl_event_pinned_bytes(ctx.handle))
         self.pinned = torch.empty(max(pb, 64), dtype=torch.uint8, pin_memory=True)
+        # the workspace as the results are viewed (its size is a multiple of 256 bytes)
+        self._base, self._words = self.ws.data_ptr(), self.ws.view(torch.int32)
+        self._floats = self.ws.view(torch.float32)
         self._h = ctypes.c_void_p()
         _check(lib().pxcl_event_bind(ctx.handle, self.ws.data_ptr(), nb, self.pinned.data_ptr(), pb,
                                      self.max_digis, _stream_ptr(stream), ctypes.byref(self._h)), "event_bind")
@@ -344,9 +351,9 @@ class Event:
     def handle(self):
         return self._h
 
-    def _view(self, ptr: int, count: int) -> torch.Tensor:
-        off = int(ptr) - self.ws.data_ptr()
-        return self.ws[off: off + 4 * count].view(torch.int32)
+    def _view(self, ptr: int, count: int, of: Optional[torch.Tensor] = None) -> torch.Tensor:
+        at = (ptr - self._base) >> 2
+        return (self._words if of is None else of)[at: at + count]
 
     def close(self):
         if self._h:
@@ -386,9 +393,9 @@ def produce(event: Event) -> ClusterResult:
     st = int(lib().pxcl_produce(event.handle, ctypes.byref(c)))
     if st in (E_NOT_READY, E_INVAL):
         raise PxclError(st, "produce")
-    return ClusterResult(st, int(c.err_bits), int(c.n_clusters), event._view(c.id, c.n_clusters),
-                         event._view(c.charge, c.n_clusters), event._view(c.size, c.n_clusters),
-                         event._view(c.digi_cluster, c.n_digis), c.stream or 0, c.done_event or 0)
+    k, view = c.n_clusters, event._view
+    return ClusterResult(st, c.err_bits, k, view(c.id, k), view(c.charge, k), view(c.size, k),
+                         view(c.digi_cluster, c.n_digis), c.stream or 0, c.done_event or 0)
 
 
 @dataclass
@@ -433,7 +440,7 @@ def hits_produce(event: Event) -> HitsResult:
     if st in (E_NOT_READY, E_INVAL):
         raise PxclError(st, "hits_produce")
     n = int(h.n_hits)
-    return HitsResult(st, n, event._view(h.x, n).view(torch.float32), event._view(h.y, n).view(torch.float32),
+    return HitsResult(st, n, event._view(h.x, n, event._floats), event._view(h.y, n, event._floats),
                       h.stream or 0, h.done_event or 0)
 
 
