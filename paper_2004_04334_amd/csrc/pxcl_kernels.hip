@@ -197,14 +197,17 @@ __device__ __forceinline__ u32 group_excl_scan(u32 v, u32 lt, u32* wsum, u32& to
     }
 }
 
-// Largest i in [0, k) with pref[i] <= t, given pref[0] <= t < pref[k].
+// The value of lane 0 in every lane (for values the whole wave holds alike: the
+// compiler then keeps them in scalar registers and branches on them uniformly).
+__device__ __forceinline__ u32 wave_uniform(u32 v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Largest i in [0, k) with pref[i] <= t, given pref[0] <= t < pref[k], t the same for the
+// whole wave: two ballots (k <= MAXB = 128) instead of a chain of LDS reads, and the event
+// behind it then comes by scalar loads.  All lanes of the wave call it.
 __device__ __forceinline__ u32 find_slot(const u32* pref, u32 k, u32 t) {
-    u32 lo = 0, hi = k;
-    while (hi - lo > 1) {
-        const u32 mid = (lo + hi) >> 1;
-        if (pref[mid] <= t) lo = mid; else hi = mid;
-    }
-    return lo;
+    const u32 lane = threadIdx.x & 63u;
+    const bool in0 = lane < k && pref[lane] <= t, in1 = lane + 64 < k && pref[lane + 64] <= t;
+    return wave_uniform(u32(__popcll(__ballot(in0 ? 1 : 0)) + __popcll(__ballot(in1 ? 1 : 0))) - 1u);
 }
 
 // What event_prefix counts per event: its digis (CNT_DIGIS), the digis of an event
@@ -439,7 +442,7 @@ __device__ __forceinline__ void word_links(const u32* bm, const u64* col, u32 c,
 // ---------------------------------------------------------------------------
 // group (digis in any order): a counting sort by module ahead of the clustering,
 // which then reads a grouped copy in the event workspace and writes every per-digi
-// output at the digi's input position.  Three kernels:
+// output at the digi's input position.  Three steps:
 //   count    per chunk of G_CH digis an LDS histogram over the modules gives each
 //            digi its rank among the chunk's digis of its module; one device atomic
 //            per (chunk, module present in it) adds the chunk's count to the module's
@@ -447,10 +450,11 @@ __device__ __forceinline__ void word_links(const u32* bm, const u64* col, u32 c,
 //            base + local rank.  The rank is parked in the per-digi output word (the
 //            clustering overwrites it).  Module ids at or above the module count set
 //            EB_RANGE and the digi takes no part.
-//   table    one workgroup per event: an exclusive scan of the module totals gives
-//            each module its first grouped position; module-table entries tagged with
-//            the launch, the present-module list in ascending module order, kept
-//            counts and totals cleared -- the segmentation kernel's outputs.
+//   table    an exclusive scan of the module totals gives each module its first grouped
+//            position; module-table entries tagged with the launch, the present-module
+//            list in ascending module order, kept counts cleared -- the segmentation
+//            kernel's outputs.  Part of the scatter kernel, or a kernel of its own for
+//            more than G_HMAX modules; the compaction clears the totals.
 //   scatter  every digi goes to first[module] + rank of the grouped copy.  What bounds it is
 //            the number of scattered stores (a wave's 64 digis go to dozens of modules), so a
 //            digi is one word: 16 events of 64,000 digis 31.7 -> 15.5 us (row, column, adc,
@@ -528,68 +532,84 @@ __global__ __launch_bounds__(G_WG) void k_group_count(LaunchArgs a) {
     }
 }
 
-__global__ __launch_bounds__(G_WG) void k_group_table(LaunchArgs a) {
-    __shared__ u32 s_wsum[G_WG / 64];
-    const u32 tid = threadIdx.x, k = num_events(a), M = a.n_modules;
-    for (u32 e = blockIdx.x; e < k; e += gridDim.x) {
-        const EventDesc E = get_event(a, e);
-        if (!(E.flags & EF_UNSORTED)) continue;  // the same event for the whole workgroup
-        const EvLayout L = ev_layout(E.cap, M);
-        u32* gcnt = ws_ptr<u32>(E, L.gcnt);
-        u32* kept = ws_ptr<u32>(E, L.kept);
-        u32* present = ws_ptr<u32>(E, L.present);
-        u32* ctl = ws_ptr<u32>(E, L.ctl);
-        ModRange* mt = ws_ptr<ModRange>(E, L.mtab);
-        const u64 tag = u64(E.epoch) << 32;
-        u32 carry = 0, pcarry = 0;
-        for (u32 base = 0; base < M; base += G_WG * G_TPM) {
-            const u32 m0 = base + tid * G_TPM;   // this thread's G_TPM consecutive modules
-            u32 cnt[G_TPM], sum = 0, pres = 0;
+// First grouped position of every module of event E: a scan of the module totals, by one
+// workgroup.  The positions go to `first` (if given, in LDS); with `write` the segmentation
+// kernel's outputs go to the event's workspace.
+__device__ __forceinline__ void group_table(const EventDesc& E, const EvLayout& L, u32 M, u32* first, bool write, u32* wsum) {
+    const u32 tid = threadIdx.x;
+    const u32* gcnt = ws_ptr<const u32>(E, L.gcnt);
+    u32* kept = ws_ptr<u32>(E, L.kept);
+    u32* present = ws_ptr<u32>(E, L.present);
+    u32* ctl = ws_ptr<u32>(E, L.ctl);
+    ModRange* mt = ws_ptr<ModRange>(E, L.mtab);
+    const u64 tag = u64(E.epoch) << 32;
+    u32 carry = 0, pcarry = 0;
+    for (u32 base = 0; base < M; base += G_WG * G_TPM) {
+        const u32 m0 = base + tid * G_TPM;       // this thread's G_TPM consecutive modules
+        u32 cnt[G_TPM], sum = 0, pres = 0;
 #pragma unroll
-            for (u32 j = 0; j < G_TPM; ++j) {
-                cnt[j] = (m0 + j < M && E.n) ? gcnt[m0 + j] : 0u;
-                sum += cnt[j];
-                pres += cnt[j] ? 1u : 0u;
-            }
-            u32 tot, ptot;
-            const u32 ex = group_excl_scan<G_WG>(sum, tid, s_wsum, tot);
-            const u32 pex = group_excl_scan<G_WG>(pres, tid, s_wsum, ptot);
-            u32 pos = carry + ex, pp = pcarry + pex;
+        for (u32 j = 0; j < G_TPM; ++j) {
+            cnt[j] = (m0 + j < M && E.n) ? gcnt[m0 + j] : 0u;
+            sum += cnt[j];
+            pres += cnt[j] ? 1u : 0u;
+        }
+        u32 tot, ptot = 0, pex = 0;
+        const u32 ex = group_excl_scan<G_WG>(sum, tid, wsum, tot);
+        if (write) pex = group_excl_scan<G_WG>(pres, tid, wsum, ptot);
+        u32 pos = carry + ex, pp = pcarry + pex;
 #pragma unroll
-            for (u32 j = 0; j < G_TPM; ++j) {
-                const u32 m = m0 + j;
-                if (m >= M) break;
+        for (u32 j = 0; j < G_TPM; ++j) {
+            const u32 m = m0 + j;
+            if (m >= M) break;
+            if (first) first[m] = pos;
+            if (write) {
                 if (cnt[j]) {
                     const u32 end = pos + cnt[j];
                     if (end <= E.n) mt[m] = ModRange{tag | pos, tag | end};
                     else atomicOr(&ctl[CTL_ERR], EB_INTERNAL);   // totals left by a launch that did not finish
                     if (pp < M) present[pp] = m;
                     ++pp;
-                    gcnt[m] = 0u;
                 }
                 kept[m] = 0u;
-                pos += cnt[j];
             }
-            carry += tot;
-            pcarry += ptot;
+            pos += cnt[j];
         }
-        if (tid == 0) {
-            const u32 slot = E.slot & 1u;
-            ctl[CTL_BIG] = 0u;
-            ctl[CTL_SCR] = 0u;
-            ctl[CTL_DEFERRED] = 0u;
-            ctl[CTL_CTR] = 0u;                   // the small kernel's ticket of this event
-            ctl[CTL_PRESENT + slot] = pcarry;
-            ctl[CTL_PRESENT + (slot ^ 1u)] = 0u;
-        }
+        carry += tot;
+        pcarry += ptot;
+    }
+    if (write && tid == 0) {
+        const u32 slot = E.slot & 1u;
+        ctl[CTL_BIG] = 0u;
+        ctl[CTL_SCR] = 0u;
+        ctl[CTL_DEFERRED] = 0u;
+        ctl[CTL_CTR] = 0u;                       // the small kernel's ticket of this event
+        ctl[CTL_PRESENT + slot] = pcarry;
+        ctl[CTL_PRESENT + (slot ^ 1u)] = 0u;
     }
 }
 
+__global__ __launch_bounds__(G_WG) void k_group_table(LaunchArgs a) {
+    __shared__ u32 s_wsum[G_WG / 64];
+    const u32 k = num_events(a);
+    for (u32 e = blockIdx.x; e < k; e += gridDim.x) {
+        const EventDesc E = get_event(a, e);
+        if (!(E.flags & EF_UNSORTED)) continue;  // the same event for the whole workgroup
+        group_table(E, ev_layout(E.cap, a.n_modules), a.n_modules, nullptr, true, s_wsum);
+    }
+}
+
+// TABLE: the first positions come from k_group_table's table.  Else (at most G_HMAX modules)
+// every workgroup scans the totals of its event itself, and the one with the event's first
+// chunk also writes the table: reading 7 KB from the L2 and two scans (~2 us) take the place
+// of a launch of one workgroup per event (6.4 us and the gap before it).
+template <bool TABLE>
 __global__ __launch_bounds__(G_WG) void k_group_scatter(LaunchArgs a) {
     __shared__ u32 s_pref[MAXB + 1];
     __shared__ u32 s_wsum[G_WG / 64];
+    __shared__ u32 s_first[TABLE ? 1 : G_HMAX];
     const u32 tid = threadIdx.x, k = num_events(a), M = a.n_modules;
     const u32 total = event_prefix<G_WG>(a, k, s_pref, s_wsum, CNT_ANY, G_SCH, 0);
+    u32 have = NOPIX;                            // the event whose positions s_first holds
     for (u32 t = blockIdx.x; t < total; t += gridDim.x) {
         const u32 e = find_slot(s_pref, k, t), c = t - s_pref[e];
         const EventDesc E = get_event(a, e);
@@ -605,26 +625,36 @@ __global__ __launch_bounds__(G_WG) void k_group_scatter(LaunchArgs a) {
 #pragma unroll
         for (u32 q = 0; q < G_SPER; ++q) {
             const u32 i = i0 + q * G_WG;
+            const u32 iv = i < E.n ? i : 0u;
             mm[q] = i < E.n ? u32(E.r_module[i]) : NOPIX;
+            if constexpr (!TABLE) pos[q] = rank[iv];
+            rr[q] = E.r_row[iv];
+            cc[q] = E.r_col[iv];
+            aa[q] = E.r_adc[iv];
+        }
+        if constexpr (!TABLE) {
+            if (e != have) {
+                lds_barrier();                   // every digi of the last chunk has its position
+                group_table(E, L, M, s_first, c == 0, s_wsum);
+                lds_barrier();
+                have = e;
+            }
         }
 #pragma unroll
         for (u32 q = 0; q < G_SPER; ++q) {
             const u32 i = i0 + q * G_WG;
             const bool v = mm[q] < M;            // past the end, or out of range (flagged by count)
-            const u32 iv = v ? i : 0u;
-            const ModRange r = mt[v ? mm[q] : 0u];
-            pos[q] = (v && u32(r.first >> 32) == E.epoch) ? u32(r.first) + rank[iv] : NOPIX;
-            if (pos[q] != NOPIX && pos[q] >= u32(r.end)) pos[q] = NOPIX;   // only after an internal error
-            rr[q] = E.r_row[iv];
-            cc[q] = E.r_col[iv];
-            aa[q] = E.r_adc[iv];
+            if constexpr (TABLE) {
+                const ModRange r = mt[v ? mm[q] : 0u];
+                pos[q] = (v && u32(r.first >> 32) == E.epoch) ? u32(r.first) + rank[v ? i : 0u] : NOPIX;
+                if (pos[q] != NOPIX && pos[q] >= u32(r.end)) pos[q] = NOPIX;   // only after an internal error
+            } else {
+                pos[q] = v ? s_first[mm[q]] + pos[q] : NOPIX;
+            }
         }
 #pragma unroll
-        for (u32 q = 0; q < G_SPER; ++q) {
-            const u32 p = pos[q];
-            if (p == NOPIX) continue;
-            rec[p] = pack_digi(rr[q], cc[q], aa[q], i0 + q * G_WG);
-        }
+        for (u32 q = 0; q < G_SPER; ++q)
+            if (pos[q] < E.n) rec[pos[q]] = pack_digi(rr[q], cc[q], aa[q], i0 + q * G_WG);   // (not below only after one)
     }
 }
 
@@ -754,9 +784,6 @@ struct Item {
     bool ok;
 };
 
-// The value of lane 0 in every lane (for values the whole wave holds alike: the
-// compiler then keeps them in scalar registers and branches on them uniformly).
-__device__ __forceinline__ u32 wave_uniform(u32 v) { return __builtin_amdgcn_readfirstlane(v); }
 template <typename T>
 __device__ __forceinline__ T PXCL_G* wave_uniform(T PXCL_G* p) {
     const u64 x = reinterpret_cast<u64>(p);
@@ -1281,11 +1308,7 @@ __global__ __launch_bounds__(WG) PXCL_WAVES_PER_EU(small_waves_per_simd<WG, MPW,
     };
     const u32 lane = lt & 63u;
     auto step_module = [&](u32 t, Next& N) {
-        N.e = 0;
-        if (k > 1) {                          // the last event whose first unit is at or before t
-            const u32 in0 = lane < k && s.pref[lane] <= t, in1 = lane + 64 < k && s.pref[lane + 64] <= t;
-            N.e = wave_uniform(u32(__popcll(__ballot(in0)) + __popcll(__ballot(in1))) - 1u);
-        }
+        N.e = k == 1 ? 0u : find_slot(s.pref, k, t);
         N.E = event_at(a, N.e);
         if (fused) {
             N.mod = t;
@@ -2149,6 +2172,8 @@ __global__ __launch_bounds__(C_WG) void k_compact(LaunchArgs a) {
         const EvLayout L = ev_layout(E.cap, M);
         u32* ctl = ws_ptr<u32>(E, L.ctl);
         const u32* kept = ws_ptr<const u32>(E, L.kept);
+        // the module totals of digis in any order are zero between launches
+        if ((E.flags & EF_UNSORTED) && part == 0 && b * C_BLK + lane < M) ws_ptr<u32>(E, L.gcnt)[b * C_BLK + lane] = 0u;
         if ((a.flags & LF_DEFER) && (ld_ag(ctl + CTL_BIG) | ld_ag(ctl + CTL_SCR)) != 0u) {
             // modules wait for the big-module kernels of a second launch: nothing is
             // compacted, the lists and error bits stay for it, the host learns why
@@ -2413,19 +2438,25 @@ int occupancy_compact() { return occ(reinterpret_cast<const void*>(k_compact), C
 
 int occupancy_group() {
     return std::min(occ(reinterpret_cast<const void*>(k_group_count), G_WG),
-                    occ(reinterpret_cast<const void*>(k_group_scatter), G_WG));
+                    std::min(occ(reinterpret_cast<const void*>(k_group_scatter<false>), G_WG),
+                             occ(reinterpret_cast<const void*>(k_group_scatter<true>), G_WG)));
 }
 u32 group_chunk() { return G_CH; }
 u32 group_scatter_chunk() { return G_SCH; }
-// The grouping kernels of the events in any order: count over `grid` workgroups,
-// the table over `grid_events`, scatter over `grid_scatter`.
+// The grouping kernels of the events in any order: count over `grid` workgroups, scatter over
+// `grid_scatter`; between them, with more modules than the scatter can hold the first
+// positions of, the table over `grid_events`.
 hipError_t launch_group(const LaunchArgs& a, u32 grid, u32 grid_events, u32 grid_scatter, hipStream_t s) {
     hipLaunchKernelGGL(k_group_count, dim3(grid), dim3(G_WG), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_group_table, dim3(grid_events), dim3(G_WG), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_group_scatter, dim3(grid_scatter), dim3(G_WG), 0, s, a);
+    if (a.n_modules > G_HMAX) {
+        hipLaunchKernelGGL(k_group_table, dim3(grid_events), dim3(G_WG), 0, s, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_group_scatter<true>, dim3(grid_scatter), dim3(G_WG), 0, s, a);
+    } else {
+        hipLaunchKernelGGL(k_group_scatter<false>, dim3(grid_scatter), dim3(G_WG), 0, s, a);
+    }
     return hipGetLastError();
 }
 hipError_t launch_segment(const LaunchArgs& a, u32 grid, hipStream_t s) {
