@@ -1482,13 +1482,21 @@ struct DenseSmem {
     u32 wsum[G / 64];
 };
 
+// This thread's index, worked out anew for every module (the second term is zero): addresses
+// that depend on the index alone would be computed before the loop over the modules, for
+// both modes, and spilled (21 registers, reloaded from memory between LDS phases).
+template <u32 WG>
+__device__ __forceinline__ u32 thread_in_loop(const Item& I) {
+    return (threadIdx.x + (I.n >> 31)) & (WG - 1u);
+}
+
 template <u32 G, u32 K>
 __device__ __forceinline__ void cluster_dense(const LaunchArgs& a, const EventDesc& E, const EvLayout& L, const Item& I,
                                               DenseSmem<G, K>& s) {
     constexpr u32 KBW = G * K / 32;
     static_assert(G >= COLS && KBW <= G, "a thread per column, and per word of kept bits");
     static_assert(G * K <= 16384, "sizes of up to 15 bits, run numbers of up to 16");
-    const u32 tid = threadIdx.x, n = I.n, st = I.st;
+    const u32 tid = thread_in_loop<G>(I), n = I.n, st = I.st;
     const u32 nq = min((n + G - 1) / G, K);
     const ModuleDigis D = module_digis(E, L, st);
     const bool hits = (E.flags & EF_HITS) != 0;
@@ -1640,7 +1648,7 @@ __device__ __forceinline__ void cluster_dense(const LaunchArgs& a, const EventDe
 // event's final charge/size arrays, which the compaction kernel overwrites later, for the
 // rest), leaving each digi's cluster in its output word; per-digi ids from that.  The passes
 // take four digis per load and test the ranges of four at once.  Like register mode it is
-// bound by the instructions of one workgroup: a serpentine 159 -> 84 us (before: unions
+// bound by the instructions of one workgroup: a serpentine 159 -> 75 us (before: unions
 // column by column, a lane per row, 60-85 us of it; one digi per load; runs looked up again
 // for the ids).
 template <u32 BW>
@@ -1650,6 +1658,7 @@ struct BigScratchSmem {
     u32 rootb[MAX_RUNS / 32];   // root runs, then kept clusters (over cluster index)
     u64 col[COLS + 2];          // entry c+1: column c's run numbers
     u16 rootp[MAX_RUNS / 32];   // roots before each word, then kept clusters before each word
+    u16 src[WPC * COLS];        // word k of column c: leftmost column of its stretch of like words
     u32 wsum[BW / 64];
 };
 
@@ -1695,7 +1704,7 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
     constexpr u32 KW = MAX_RUNS / 32, KPT = (KW + BW - 1) / BW;
     constexpr u32 SPAN = 4 * UNR * BW;                     // digis per step
     static_assert(BW >= COLS, "a thread per column");
-    const u32 tid = threadIdx.x, n = I.n, st = I.st;
+    const u32 tid = thread_in_loop<BW>(I), n = I.n, st = I.st;
     u32* cid = (u32*)E.o_id + st;       // per cluster: id (or -1 once cut)
     u32* cch = (u32*)E.o_charge + st;   // per cluster: charge
     u32* csz = (u32*)E.o_size + st;     // per cluster: size
@@ -1775,8 +1784,35 @@ __device__ __forceinline__ void cluster_scratch(const LaunchArgs& a, const Event
         if (tid < COLS) s.col[tid + 1] = e | run;
     }
     lds_barrier();
-    for (u32 u = tid; u < WORDS; u += BW)                       // first parents
-        word_parents(s.bm, s.col, u / WPC, u % WPC, [&](u32 run, u32 parent) { st_wg(&s.par[run], parent); });
+    // Stretches of columns that hold the same 32 rows (and the same bit above them): their run
+    // starts are the same too, and the runs that start at one row touch from column to column,
+    // so each starts under the stretch's first one instead of its left neighbour.  A wave per
+    // row of words, 1.3 us.  Chains along rows are as long as the module: 80 of them (a
+    // serpentine along rows) took 24 us to flatten, now 17.
+    for (u32 k = wv; k < WPC; k += BW / 64) {
+        u32 carry = 0;
+#pragma unroll
+        for (u32 g = 0; g < (COLS + 63) / 64; ++g) {
+            const u32 c = g * 64 + lane, cc = min(c, COLS - 1);
+            const u32* w = &s.bm[BM_FRONT + cc * WPC + k];
+            const u32 b = w[0], l = *(w - WPC), ab = k ? *(w - 1) >> 31 : 0u, al = k ? *(w - 1 - WPC) >> 31 : 0u;
+            const u64 m = __ballot(c == 0 || b == 0u || b != l || ab != al ? 1 : 0), upto = m & ((2ull << lane) - 1ull);
+            const u32 first = upto ? g * 64 + 63u - u32(__builtin_clzll(upto)) : carry;
+            if (c < COLS) s.src[k * COLS + c] = u16(first);
+            carry = m ? g * 64 + 63u - u32(__builtin_clzll(m)) : carry;
+        }
+    }
+    lds_barrier();
+    for (u32 u = tid; u < WORDS; u += BW) {                     // first parents
+        const u32 c = u / WPC, k = u % WPC, src = s.src[k * COLS + c];
+        if (src == c) {
+            word_parents(s.bm, s.col, c, k, [&](u32 run, u32 parent) { st_wg(&s.par[run], parent); });
+        } else {
+            const ColWord x = col_word(s.bm, s.col, c, k);
+            const u32 n_st = u32(__popc(x.st)), r0 = runs_before(s.col[src + 1], k) + (x.b & (x.above >> 31));
+            for (u32 i = 0; i < n_st; ++i) st_wg(&s.par[x.r0 + i], r0 + i);
+        }
+    }
     lds_barrier();
     // Every run points at its root.  A thread moves only its own runs' parents, each to an
     // ancestor, so what it stores last (the root) stands; others' moves double the steps.
@@ -2106,7 +2142,7 @@ __global__ __launch_bounds__(B_WG) void k_big(LaunchArgs a) {
         const bool scr = t < xtotal;
         const Item I = wave_uniform(big_item(a, scr ? s_xpref : s_pref, k, scr ? t : t - xtotal, scr));
         if (I.ok) {                           // the same for the whole workgroup
-            const EventDesc E = get_event(a, I.e);
+            const EventDesc& E = *event_at(a, I.e);
             const EvLayout L = ev_layout(E.cap, a.n_modules);
             if (scr) cluster_scratch<S_WG>(a, E, L, I, s.x);
             else cluster_dense<B_WG, K_BIG>(a, E, L, I, s.d);
