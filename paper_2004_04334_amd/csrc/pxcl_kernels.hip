@@ -885,6 +885,7 @@ __device__ __forceinline__ void cluster_regs(const LaunchArgs& a, const EventDes
                                              Mid mid) {
     static_assert(G * K <= 16384, "sizes of up to 15 bits, run numbers of up to 16");
     constexpr u32 KBW = G * K / 32, CPT = (COLS + G - 1) / G;
+    lt = (lt + (I.n >> 31)) & (G - 1u);                    // worked out anew for every module, as in thread_in_loop
     const bool act = I.ok;
     const u32 nq = act ? min((I.n + G - 1) / G, K) : 0u;   // slots that may hold a digi
     u32 err = 0, dup = 0, starts = 0;                      // starts, bit q: slot q starts its run
