@@ -41,9 +41,7 @@ import numpy as np  # noqa: E402
 HBM_PEAK_GBS = 8000.0
 KERNELS = ["segment", "big", "small", "compact", "hits"]
 KERNEL_SYMBOLS = {"segment": "k_segment", "big": "k_big", "small": "k_small", "compact": "k_compact", "hits": "k_hits"}
-# kernels behind each timing slot: the big-module slot times register and scratch mode
-KERNEL_PARTS = {"big": ["k_big", "k_scratch"]}
-ALL_SYMBOLS = list(KERNEL_SYMBOLS.values()) + ["k_scratch"]
+ALL_SYMBOLS = list(KERNEL_SYMBOLS.values())
 METRIC = "events/s + digis/s clustered (frac HBM peak); p50/p99 event latency; host block time"
 
 COPY_BYTES = 1 << 30
@@ -72,22 +70,13 @@ def kernel_src_sha() -> str:
 
 def load_traffic(workload: str, kernel: str, shape):
     """HBM traffic per launch from the committed rocprofv3 counter summaries of the
-    kernels behind a timing slot at the run's small-kernel shape, if they were taken on
-    the current kernel source (a kernel without a summary did not run in that
-    workload; no summary at all: None)."""
-    total, found = 0, False
-    if not os.path.exists(os.path.join(ROOT, "profiles", f"kernels_{profile_tag(workload, shape)}.txt")):
+    kernel behind a timing slot at the run's small-kernel shape, if they were taken on
+    the current kernel source (else None)."""
+    p = os.path.join(ROOT, "profiles", f"pmc_{KERNEL_SYMBOLS[kernel]}_{profile_tag(workload, shape)}.json")
+    if not os.path.exists(p):
         return None
-    for sym in KERNEL_PARTS.get(kernel, [KERNEL_SYMBOLS[kernel]]):
-        p = os.path.join(ROOT, "profiles", f"pmc_{sym}_{profile_tag(workload, shape)}.json")
-        if not os.path.exists(p):
-            continue
-        d = json.load(open(p))
-        if d.get("kernel_src_sha") != kernel_src_sha():
-            return None
-        total += d.get("traffic_bytes_per_launch", 0)
-        found = True
-    return total if found else None
+    d = json.load(open(p))
+    return d.get("traffic_bytes_per_launch") if d.get("kernel_src_sha") == kernel_src_sha() else None
 
 
 def profile_kernel_us(workload: str, shape):
@@ -121,11 +110,10 @@ def roofline(ctx, bytes_per_launch: float, workload: str):
     t = avg[dom] * 1e-3
     achieved = bytes_per_launch / t / 1e9 if t > 0 else 0.0
     pipe = sum(avg.values()) * 1e-3
-    parts = KERNEL_PARTS.get(dom, [KERNEL_SYMBOLS[dom]])
     kt = profile_kernel_us(workload, tuple(ctx.kernel_config()))
-    kt_us = sum(kt.get(x, 0.0) for x in parts) if kt else None
+    kt_us = kt.get(KERNEL_SYMBOLS[dom], 0.0) if kt else None
     return {
-        "bound": "hbm", "kernel": "+".join(parts), "achieved": round(achieved, 2),
+        "bound": "hbm", "kernel": KERNEL_SYMBOLS[dom], "achieved": round(achieved, 2),
         "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 5),
         "traffic": load_traffic(workload, dom, tuple(ctx.kernel_config())),
         "algorithmic_bytes_per_launch": int(bytes_per_launch),
@@ -476,12 +464,12 @@ def bench_batch(px, torch, args, evs, steps, warmup, timed=True):
         h = _batched(px, torch, args, evs, 8, 64, "batch", BATCH_DESC, steps, warmup, hint=True)
         r["with_size_hint"] = {"value": round(h["value"], 2), "digis_per_s": round(h["digis_per_s"], 1),
                                "note": "every event's largest module passed as max_module_digis (host-side "
-                                       "bincount outside the timed region): the scratch-mode kernel is skipped"}
+                                       "bincount outside the timed region): no workgroups for the scratch mode"}
         u = _batched(px, torch, args, shuffled(evs), 8, 64, "batch", BATCH_DESC, steps, warmup, any_order=True)
         r["any_order"] = {"value": round(u["value"], 2), "digis_per_s": round(u["digis_per_s"], 1),
                           "kernel_mean_us": u["roofline"]["kernel_mean_us"],
                           "note": "the same events with their digis shuffled, grouped by module on the device "
-                                  "(counting sort: count, table, scatter) in the segment slot"}
+                                  "(counting sort: count, scatter) in the segment slot"}
     return r
 
 
@@ -791,13 +779,13 @@ def main():
                                                      hint=True, shape=shape)[k]
                                       for k in ("value", "digis_per_s", "lat_p50_us", "lat_p99_us")})
         a["with_size_hint"]["note"] = ("every event's largest module passed as max_module_digis (host-side "
-                                       "bincount outside the timed region): neither big-module kernel is launched")
+                                       "bincount outside the timed region): the big-module kernel is not launched")
         dfr = bench_async(px, torch, args, evsets["async"], SUB_STEPS["async"], defer=True, shape=shape)
         a["with_deferred_big_kernels"] = _round({k: dfr[k] for k in ("value", "digis_per_s", "lat_p50_us",
                                                                       "lat_p99_us", "host_blocked_us_per_event")})
         a["with_deferred_big_kernels"]["kernel_mean_us"] = dfr["roofline"]["kernel_mean_us"]
         a["with_deferred_big_kernels"]["note"] = (
-            "no size hint: every event is launched without the big-module kernels, which the library queues in a "
+            "no size hint: every event is launched without the big-module kernel, which the library queues in a "
             "second launch only when the small kernel lists a module for them (none in these events); results are "
             "final at the callback")
         hs = bench_async(px, torch, args, evsets["async"], SUB_STEPS["async"] // 4, where="pinned", shape=shape)
@@ -813,7 +801,7 @@ def main():
         a["any_order"] = _round({k: u[k] for k in ("value", "digis_per_s", "lat_p50_us", "lat_p99_us")})
         a["any_order"]["kernel_mean_us"] = u["roofline"]["kernel_mean_us"]
         a["any_order"]["note"] = ("the same events with their digis shuffled, grouped by module on the device "
-                                  "(counting sort: count, table, scatter) in the segment slot")
+                                  "(counting sort: count, scatter) in the segment slot")
         subs["async"] = sub_record(a, evsets["async"], args)
         print("bench: plain", file=sys.stderr, flush=True)
         p = bench_plain(px, torch, args, evsets["plain"], SUB_STEPS["plain"])

@@ -110,8 +110,8 @@ typedef struct {
  * unmodified until the done callback has fired.
  * max_module_digis: optional upper bound on the digis of any one module (0 =
  * unknown).  When it is at most the small-module kernel's capacity (workgroup size /
- * modules per workgroup * 8 digis), neither big-module kernel is launched; when it
- * is at most 16,384 the scratch-mode kernel is not launched.  A module above the
+ * modules per workgroup * 8 digis), the big-module kernel is not launched; when it
+ * is at most 16,384 no workgroups are launched for its scratch mode.  A module above the
  * bound is then not clustered and the event fails with PXCL_E_HINT. */
 typedef struct {
     const uint16_t* module;
@@ -130,7 +130,7 @@ typedef struct {
  * unfinished; the completion thread then queues the big-module kernels and the
  * compaction on the event's stream (a second launch, recording the completion event
  * again) before the callback fires.  Events without such modules finish in the one
- * launch, sparing the two big-module launches, which wait for whole compute units.
+ * launch, sparing the big-module launch, which waits for whole compute units.
  * The results are final only when the callback fires: work queued after the acquire
  * on the same stream is not ordered after the second launch, and pxcl_hits_enqueue
  * and pxcl_copy_to_host return PXCL_E_BUSY while the event is in flight.  With
@@ -217,7 +217,8 @@ int pxcl_event_unbind(pxcl_event* ev);
 uint32_t pxcl_event_capacity(const pxcl_event* ev);
 
 /* Enqueue the clustering of one event on `stream` (hipStream_t): an async copy of
- * host digis into the slot (PXCL_WHERE_HOST), the device kernels (a single event
+ * host digis into the slot (PXCL_WHERE_HOST; one kernel moves the four arrays when they
+ * are 8-byte aligned and not too large), the device kernels (a single event
  * needs no segmentation kernel: the small-module kernel finds every module's digis
  * by search and checks the module ids itself), and a completion event that the
  * context's completion thread polls.  Returns without waiting for the device.  Synchronous errors
@@ -285,7 +286,8 @@ int pxcl_hits_wait(pxcl_event* ev);
 /* Sec. 4.3: device results go to the host only when a CPU consumer asks.
  * pxcl_copy_to_host queues asynchronous device-to-host copies of the event's kept
  * clusters (and, if digi_cluster is set, its per-digi ids; if x and y are set, its
- * hits, which must have been queued) into caller-owned pinned buffers, on `stream`,
+ * hits, which must have been queued) into caller-owned pinned buffers, on `stream`
+ * (one kernel for all arrays, as for host digis),
  * waiting for the event (and the hits) across streams like pxcl_hits_enqueue.  The
  * cluster arrays must hold `capacity` >= the event's kept clusters once it is
  * complete, or >= its digis while it may be in flight (PXCL_E_CAPACITY otherwise).
