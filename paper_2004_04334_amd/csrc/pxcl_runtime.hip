@@ -289,9 +289,10 @@ bool digis_ok(const pxcl_digis* in) {
 }
 
 // Arrays to copy between pinned host memory and the device, on a stream: by one kernel when
-// every host end is 8-byte aligned memory that the device can address (the workspace's ends
-// are 256-byte aligned) and the whole is small enough for its start to matter, else (views at
-// odd offsets, pageable memory, large events) by one copy command each.
+// every host end is 8-byte aligned memory that the device can address, from its first byte to
+// its last (the workspace's ends are 256-byte aligned), and the whole is small enough for its
+// start to matter, else (views at odd offsets, pageable memory, large events) by one copy
+// command each.
 struct HostCopies {
     struct One {
         void* dst;
@@ -311,7 +312,10 @@ struct HostCopies {
         for (u32 i = 0; i < n && kernel; ++i) {
             void* host = to_host ? one[i].dst : const_cast<void*>(one[i].src);
             void* dev = nullptr;
-            if ((reinterpret_cast<uintptr_t>(host) & 7u) || hipHostGetDevicePointer(&dev, host, 0) != hipSuccess || !dev) {
+            void* last = nullptr;                          // of an array pinned in part only: not to be had
+            if ((reinterpret_cast<uintptr_t>(host) & 7u) || hipHostGetDevicePointer(&dev, host, 0) != hipSuccess || !dev ||
+                hipHostGetDevicePointer(&last, static_cast<u8*>(host) + one[i].bytes - 1, 0) != hipSuccess ||
+                last != static_cast<u8*>(dev) + one[i].bytes - 1) {
                 (void)hipGetLastError();
                 kernel = false;
                 break;
