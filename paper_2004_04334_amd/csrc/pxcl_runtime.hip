@@ -288,11 +288,25 @@ bool digis_ok(const pxcl_digis* in) {
     return true;
 }
 
+// What a host address is: one query for its kind, one for the allocation around it.
+HostMemory host_memory(void* host) {
+    HostMemory m{};
+    hipPointerAttribute_t at{};
+    void* base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, host) == hipSuccess && at.type == hipMemoryTypeHost && at.devicePointer &&
+        hipMemGetAddressRange(&base, &size, at.devicePointer) == hipSuccess) {
+        m = HostMemory{true, reinterpret_cast<u64>(at.devicePointer), reinterpret_cast<u64>(base), size};
+    } else {
+        (void)hipGetLastError();
+    }
+    return m;
+}
+
 // Arrays to copy between pinned host memory and the device, on a stream: by one kernel when
-// every host end is 8-byte aligned memory that the device can address, from its first byte to
-// its last (the workspace's ends are 256-byte aligned), and the whole is small enough for its
-// start to matter, else (views at odd offsets, pageable memory, large events) by one copy
-// command each.
+// copy_kernel_takes every host end (the workspace's ends are 256-byte aligned) and the whole
+// is small enough for its start to matter, else (views at odd offsets, pageable memory, large
+// events) by one copy command each.
 struct HostCopies {
     struct One {
         void* dst;
@@ -311,15 +325,12 @@ struct HostCopies {
         bool kernel = bytes <= KERNEL_COPY_BYTES;
         for (u32 i = 0; i < n && kernel; ++i) {
             void* host = to_host ? one[i].dst : const_cast<void*>(one[i].src);
-            void* dev = nullptr;
-            void* last = nullptr;                          // of an array pinned in part only: not to be had
-            if ((reinterpret_cast<uintptr_t>(host) & 7u) || hipHostGetDevicePointer(&dev, host, 0) != hipSuccess || !dev ||
-                hipHostGetDevicePointer(&last, static_cast<u8*>(host) + one[i].bytes - 1, 0) != hipSuccess ||
-                last != static_cast<u8*>(dev) + one[i].bytes - 1) {
-                (void)hipGetLastError();
+            const HostMemory m = host_memory(host);
+            if (!copy_kernel_takes(reinterpret_cast<u64>(host), one[i].bytes, m)) {
                 kernel = false;
                 break;
             }
+            void* dev = reinterpret_cast<void*>(m.dev);
             c.src[i] = static_cast<const u64*>(to_host ? one[i].src : dev);
             c.dst[i] = static_cast<u64*>(to_host ? dev : one[i].dst);
             c.first[i] = u32(words);
