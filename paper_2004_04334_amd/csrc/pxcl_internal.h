@@ -157,18 +157,20 @@ struct CopyArgs {
     u32 n;
 };
 
-// What the runtime says of a host address: memory it allocated (pinned), and where the
-// device finds the address and the allocation around it.
+// What the runtime says of a host address: memory it allocated (pinned), coherent unless
+// asked for otherwise, and where the device finds the address and the allocation around it.
 struct HostMemory {
-    bool pinned;
+    bool pinned, coherent;
     u64 dev, base, size;
 };
 // The copy kernel may move `bytes` from or to `host`: 8-byte aligned, and every byte in one
 // allocation that the device can address (the ends alone do not tell: two pinned blocks with
-// anything between them have both).
+// anything between them have both).  Coherent, since the kernel's accesses make nothing else
+// visible: the device may hold non-coherent memory in its caches across kernels, so the host's
+// new values could be missed, and the results could reach the host after the callback.
 inline bool copy_kernel_takes(u64 host, size_t bytes, const HostMemory& m) {
-    return m.pinned && (host & 7u) == 0 && (m.dev & 7u) == 0 && m.dev >= m.base && m.dev - m.base <= m.size &&
-           bytes <= m.size - (m.dev - m.base);
+    return m.pinned && m.coherent && (host & 7u) == 0 && (m.dev & 7u) == 0 && m.dev >= m.base &&
+           m.dev - m.base <= m.size && bytes <= m.size - (m.dev - m.base);
 }
 
 PXCL_HD constexpr size_t al256(size_t x) { return (x + 255) & ~size_t(255); }

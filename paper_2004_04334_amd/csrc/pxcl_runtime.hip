@@ -296,7 +296,8 @@ HostMemory host_memory(void* host) {
     size_t size = 0;
     if (hipPointerGetAttributes(&at, host) == hipSuccess && at.type == hipMemoryTypeHost && at.devicePointer &&
         hipMemGetAddressRange(&base, &size, at.devicePointer) == hipSuccess) {
-        m = HostMemory{true, reinterpret_cast<u64>(at.devicePointer), reinterpret_cast<u64>(base), size};
+        m = HostMemory{true, (at.allocationFlags & hipHostMallocNonCoherent) == 0, reinterpret_cast<u64>(at.devicePointer),
+                       reinterpret_cast<u64>(base), size};
     } else {
         (void)hipGetLastError();
     }
@@ -306,7 +307,7 @@ HostMemory host_memory(void* host) {
 // Arrays to copy between pinned host memory and the device, on a stream: by one kernel when
 // copy_kernel_takes every host end (the workspace's ends are 256-byte aligned) and the whole
 // is small enough for its start to matter, else (views at odd offsets, pageable memory, large
-// events) by one copy command each.
+// events, non-coherent memory) by one copy command each.
 struct HostCopies {
     struct One {
         void* dst;

@@ -1,6 +1,7 @@
 """Which host arrays the copy kernel may move, asked of the library's own rule with made-up
 answers of the runtime: it reads every byte between an array's ends, so all of them must lie
-in one allocation that the device can address."""
+in one allocation that the device can address, and its accesses are coherent with the host's
+only in coherent memory."""
 from __future__ import annotations
 
 import os
@@ -14,9 +15,9 @@ MAIN = """
 #include <cstdio>
 #include "pxcl_internal.h"
 int main() {
-    unsigned long long host, bytes, pinned, dev, base, size;
+    unsigned long long host, bytes, pinned, dev, base, size;   // pinned: 1, and non-coherent: 2
     while (scanf("%llu %llu %llu %llu %llu %llu", &host, &bytes, &pinned, &dev, &base, &size) == 6)
-        printf("%d\\n", pxcl::copy_kernel_takes(host, bytes, pxcl::HostMemory{pinned != 0, dev, base, size}) ? 1 : 0);
+        printf("%d\\n", pxcl::copy_kernel_takes(host, bytes, pxcl::HostMemory{pinned != 0, pinned != 2, dev, base, size}) ? 1 : 0);
 }
 """
 P = 1 << 20                       # a block of 4,096 bytes at P, the device's view of it at P + D
@@ -32,6 +33,7 @@ CASES = [
     ("at the block's end", (P + 4096, 8, 1, P + D + 4096, P + D, 4096), 0),
     ("off 8-byte alignment", (P + 2, 64, 1, P + D + 2, P + D, 4096), 0),
     ("the device's view off alignment", (P, 64, 1, P + D + 4, P + D, 4096), 0),
+    ("non-coherent", (P, 4096, 2, P + D, P + D, 4096), 0),
     ("pageable", (P, 64, 0, 0, 0, 0), 0),
     ("pageable inside what an earlier answer held", (P, 64, 0, P + D, P + D, 4096), 0),
 ]
