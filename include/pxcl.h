@@ -424,7 +424,9 @@ typedef struct {
     uint32_t max_batch;          /* events per launch (<= each batch's capacity) */
     uint32_t n_cpu_threads;
     uint32_t cpu_task_ns;
-    uint32_t flags;              /* PXCL_BATCH_GRAPH | PXCL_BATCH_DEFER_BIG */
+    uint32_t flags;              /* PXCL_BATCH_GRAPH | PXCL_BATCH_DEFER_BIG (batches may defer:
+                                    while several in a row have needed their second launch,
+                                    nearly all launch every kernel at once; same results) */
     uint64_t seed;
     uint32_t max_inflight;       /* batches on the device at once (0 = n_batches) */
     uint32_t batch_delay_us;     /* 0: a batch starts as soon as fewer than max_inflight are on

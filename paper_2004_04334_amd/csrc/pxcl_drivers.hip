@@ -41,6 +41,7 @@ namespace pxcl {
 bool cluster_config_valid(u32 wg, u32 mpw);
 const std::string& ctx_arch(const pxcl_ctx* c);
 int ctx_device(const pxcl_ctx* c);
+bool batch_second(const pxcl_batch* b);
 void ctx_place_completer(pxcl_ctx* c, const void* cpus);
 }  // namespace pxcl
 
@@ -267,9 +268,10 @@ struct SlotPool {
 
 struct ServeState;
 
-
 struct BatchCtx {
     ServeState* S;
+    const pxcl_batch* b;
+    bool deferred;                      // the launch in flight left out the big-module kernel
     u32 bi;
     u32 k;
     u32 req[MAXB];
@@ -289,12 +291,14 @@ struct ServeState {
     Request* req = nullptr;
     clk::time_point t0;
     std::atomic<int> dispatch_wake{0};  // a batch completed: the dispatcher may launch
+    DeferChoice defer;                  // asked by the dispatcher, told by the completion thread
 };
 
 void serve_batch_done(void* user, int32_t) {
     BatchCtx* bc = static_cast<BatchCtx*>(user);
     ServeState* S = bc->S;
     S->dispatch_wake.store(1, std::memory_order_release);
+    if (bc->deferred) S->defer.done(batch_second(bc->b));
     const double now = us_since(S->t0, clk::now());
     for (u32 i = 0; i < bc->k; ++i) {
         S->req[bc->req[i]].done_us = now;
@@ -424,7 +428,7 @@ extern "C" int pxcl_serve(pxcl_ctx* ctx, void* d_arena, size_t arena_bytes, void
     u32 released_head = 0;
     S.batch_free_mask.store((n_batches >= 32 ? 0xFFFFFFFFu : ((1u << n_batches) - 1u)));
     std::vector<BatchCtx> bctx(n_batches);
-    for (u32 b = 0; b < n_batches; ++b) { bctx[b].S = &S; bctx[b].bi = b; bctx[b].k = 0; }
+    for (u32 b = 0; b < n_batches; ++b) bctx[b] = BatchCtx{&S, batches[b], false, b, 0, {}};
     std::vector<double> lat(o->n_requests, 0.0);
     std::atomic<u64> blocked_ns{0}, tasks{0}, batches_launched{0};
     std::atomic<u32> errors{0}, inflight{0}, max_inflight{0};
@@ -574,8 +578,9 @@ extern "C" int pxcl_serve(pxcl_ctx* ctx, void* d_arena, size_t arena_bytes, void
             bc.k = k;
             const double lnow = us_since(t0, a0);
             for (u32 i = 0; i < k; ++i) req[bc.req[i]].launch_us = lnow;
-            const int r = pxcl_acquire_batch(batches[b], bev.data(), bin.data(), k, s, serve_batch_done, &bc,
-                                             o->flags);
+            bc.deferred = (o->flags & PXCL_BATCH_DEFER_BIG) != 0 && S.defer.next();
+            const u32 bflags = bc.deferred ? o->flags : o->flags & ~PXCL_BATCH_DEFER_BIG;
+            const int r = pxcl_acquire_batch(batches[b], bev.data(), bin.data(), k, s, serve_batch_done, &bc, bflags);
             blocked_ns.fetch_add(u64(std::chrono::duration_cast<std::chrono::nanoseconds>(clk::now() - a0).count()));
             if (r != PXCL_OK) { err_rc.store(r); break; }
             batches_launched.fetch_add(1);

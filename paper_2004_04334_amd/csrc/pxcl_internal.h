@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #if defined(__HIPCC__)
 #define PXCL_HD __host__ __device__
 #else
@@ -172,6 +174,30 @@ inline bool copy_kernel_takes(u64 host, size_t bytes, const HostMemory& m) {
     return m.pinned && m.coherent && (host & 7u) == 0 && (m.dev & 7u) == 0 && m.dev >= m.base &&
            m.dev - m.base <= m.size && bytes <= m.size - (m.dev - m.base);
 }
+
+// Which of a server's batches defer the big-module kernel, when it may: all of them, until
+// DEFER_LATE in a row needed their second launch; then one in DEFER_RETRY tries again, and the
+// others launch everything at once.  A second launch is queued only when the completion thread
+// has seen the first one end, and whether most batches need it depends on the small kernel's
+// capacity at the shape in use.  10,000 requests of 10k-200k digis at 100 / 180 / 250 k/s, nearly
+// all with a module above 2,048 digis, p50: at 256x1 (capacity 2,048) 185 / 238 / 350 us with
+// every batch deferred, 137 / 190 / 290 with none; at 512x1 (4,096: none needs a second launch)
+// 93 / 160 / 480 deferred, 113 / 250 / 1,400 not.
+constexpr u32 DEFER_LATE = 3, DEFER_RETRY = 256;
+struct DeferChoice {
+    std::atomic<u32> late{0};   // deferred batches in a row that needed their second launch
+    u32 whole = 0;              // batches since the last deferred one
+    bool next() {               // of one thread
+        if (late.load(std::memory_order_relaxed) < DEFER_LATE) return true;
+        if (++whole < DEFER_RETRY) return false;
+        whole = 0;
+        return true;
+    }
+    void done(bool second) {    // of a deferred batch; of one thread
+        const u32 n = late.load(std::memory_order_relaxed);
+        late.store(second ? (n < DEFER_LATE ? n + 1 : n) : 0u, std::memory_order_relaxed);
+    }
+};
 
 PXCL_HD constexpr size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 

@@ -205,6 +205,7 @@ struct pxcl_batch {
     // arguments and grids, and whether the first launch's completion is pending
     hipStream_t stream = nullptr;
     bool defer_first = false;
+    bool second = false;      // the last launch needed a second one
     LaunchArgs defer_args{};
     u32 defer_grid_b = 1, defer_grid_x = 1, defer_grid_c = 1;
 };
@@ -490,6 +491,7 @@ bool batch_complete(void* p) {
             any = __atomic_load_n(&ev->hs[HS_EPOCH], __ATOMIC_ACQUIRE) == ev->epoch &&
                   (static_cast<volatile u32*>(ev->hs)[HS_ERR] & EB_DEFER) != 0;
         }
+        b->second = any;
         if (any && relaunch_deferred(b)) return false;
     }
     int32_t bst = PXCL_OK;
@@ -1436,6 +1438,7 @@ extern "C" int pxcl_acquire_batch(pxcl_batch* b, pxcl_event* const* evs, const p
     // deferred big-module kernels: a second launch (big-module kernels, compaction of
     // the events the first one left) only if some event lists a module for them
     b->defer_first = (flags & PXCL_BATCH_DEFER_BIG) != 0;
+    b->second = false;
     if (b->defer_first) lflags |= LF_NO_BIG | LF_NO_SCRATCH | LF_DEFER;
     b->stream = s;
     if (e == hipSuccess) {
@@ -1521,6 +1524,8 @@ extern "C" const char* pxcl_version(void) { return "pxcl 0.1 gfx950"; }
 namespace pxcl {
 u32 event_n(const pxcl_event* ev) { return ev->n; }
 hipEvent_t batch_done_event(const pxcl_batch* b) { return b->done_ev; }
+// For the batch's callback: the launch it completes needed a second one (deferred kernels).
+bool batch_second(const pxcl_batch* b) { return b->second; }
 const std::string& ctx_arch(const pxcl_ctx* c) { return c->arch; }
 int ctx_device(const pxcl_ctx* c) { return c->device; }
 // Restrict the context's completion thread to `cpus` (a cpu_set_t), or to every CPU of
