@@ -110,9 +110,10 @@ typedef struct {
  * unmodified until the done callback has fired.
  * max_module_digis: optional upper bound on the digis of any one module (0 =
  * unknown).  When it is at most the small-module kernel's capacity (workgroup size /
- * modules per workgroup * 8 digis), the big-module kernel is not launched; when it
- * is at most 16,384 no workgroups are launched for its scratch mode.  A module above the
- * bound is then not clustered and the event fails with PXCL_E_HINT. */
+ * modules per workgroup * 8 digis), the big-module kernel is not launched, and an
+ * event with a module above that capacity fails with PXCL_E_HINT.  A bound between the
+ * capacity and 16,384 launches what no bound does; an event with a module above 16,384
+ * digis then fails with PXCL_E_HINT.  The modules concerned are not clustered. */
 typedef struct {
     const uint16_t* module;
     const uint16_t* row;

@@ -80,7 +80,7 @@ constexpr u32 LF_NO_BIG = 1;     // the big-module kernel is not launched (size 
 constexpr u32 LF_SEG_WIDE = 2;   // segmentation in wide chunks
 constexpr u32 LF_FUSED = 4;      // one event, no segmentation kernel: the small kernel
                                  // finds every module's digis by search
-constexpr u32 LF_NO_SCRATCH = 8; // no module for the scratch mode (size hint)
+constexpr u32 LF_NO_SCRATCH = 8; // no module above BIG_RCAP digis (size hint): one is an EB_HINT
 constexpr u32 LF_GROUP = 16;     // some event is in any order: the grouping kernels run first
 constexpr u32 LF_NO_SEG = 32;    // no event is grouped by module: no segmentation kernel
 constexpr u32 LF_DEFER = 64;     // with LF_NO_BIG | LF_NO_SCRATCH: modules above the small

@@ -2507,11 +2507,10 @@ hipError_t launch_small(u32 wg, u32 mpw, const LaunchArgs& a, u32 grid, hipStrea
     hipLaunchKernelGGL(f, dim3(grid), dim3(wg), 0, s, a);
     return hipGetLastError();
 }
-// The big-module kernel: workgroups for `grid` register-mode and `grid_scratch` scratch-mode
-// modules (none of those with LF_NO_SCRATCH); with fewer, modules wait for a ticket.
-hipError_t launch_big(const LaunchArgs& a, u32 grid, u32 grid_scratch, hipStream_t s) {
-    const u32 g = std::max(grid, (a.flags & LF_NO_SCRATCH) ? 1u : grid_scratch);
-    hipLaunchKernelGGL(k_big, dim3(g), dim3(B_WG), 0, s, a);
+// The big-module kernel: workgroups for `grid` listed modules of either mode; with fewer,
+// modules wait for a ticket.
+hipError_t launch_big(const LaunchArgs& a, u32 grid, hipStream_t s) {
+    hipLaunchKernelGGL(k_big, dim3(grid), dim3(B_WG), 0, s, a);
     return hipGetLastError();
 }
 u32 compact_waves_per_block(u32 waves, u32 blocks) { return compact_split(waves, blocks); }

@@ -38,7 +38,7 @@ int occupancy_big();
 int occupancy_compact();
 hipError_t launch_segment(const LaunchArgs& a, u32 grid, hipStream_t s);
 hipError_t launch_small(u32 wg, u32 mpw, const LaunchArgs& a, u32 grid, hipStream_t s);
-hipError_t launch_big(const LaunchArgs& a, u32 grid, u32 grid_scratch, hipStream_t s);
+hipError_t launch_big(const LaunchArgs& a, u32 grid, hipStream_t s);
 hipError_t launch_compact(const LaunchArgs& a, u32 grid, hipStream_t s);
 u32 compact_waves_per_block(u32 waves, u32 blocks);
 int occupancy_hits();
@@ -150,7 +150,7 @@ struct pxcl_event {
     bool defer = false;
     bool defer_first = false;         // the first launch's completion is pending
     LaunchArgs defer_args{};
-    u32 defer_grid_b = 1, defer_grid_x = 1, defer_grid_c = 1;
+    u32 defer_grid_b = 1, defer_grid_c = 1;
     u32 slot = 0;                     // launch parity of the last launch
     bool dirty = false;               // a launch failed to queue or reported an error: clear
                                       // the control words, grouping counts and hit sums first
@@ -207,7 +207,7 @@ struct pxcl_batch {
     bool defer_first = false;
     bool second = false;      // the last launch needed a second one
     LaunchArgs defer_args{};
-    u32 defer_grid_b = 1, defer_grid_x = 1, defer_grid_c = 1;
+    u32 defer_grid_b = 1, defer_grid_c = 1;
 };
 
 // ---------------------------------------------------------------------------
@@ -216,7 +216,7 @@ struct pxcl_batch {
 namespace {
 
 struct Grids {
-    u32 a, b, s, c, x;   // segment, big, small, compact, scratch
+    u32 a, b, s, c;      // segment, big, small, compact
     u32 g, ge, gs;       // grouping of digis in any order: count, table, scatter
 };
 
@@ -238,12 +238,9 @@ Grids grids_for(const pxcl_ctx* ctx, u32 wg, u32 mpw, u64 digis, u64 present, u3
     const u64 fb = ncu * (u64)ctx->occ_l;
     const u64 fs = ncu * (u64)ctx->occ_s[31 - __builtin_clz(wg) - 6][mpw];
     const u64 fc = ncu * (u64)ctx->occ_c;
-    // workgroups for modules above BIG_RCAP digis, rare outliers (one per stress event): at
-    // most a quarter of the chip; they count only in launches with next to no others
-    const u64 fx = std::min<u64>(fb, std::max<u64>(ncu / 4, 1));
     const u64 fg = ncu * (u64)ctx->occ_g;
     if (full) {
-        g.a = u32(fa); g.b = u32(fb); g.s = u32(fs); g.c = u32(fc); g.x = u32(fx);
+        g.a = u32(fa); g.b = u32(fb); g.s = u32(fs); g.c = u32(fc);
         g.g = u32(fg); g.ge = u32(std::min<u64>(ncu, MAXB)); g.gs = u32(fg);
         return g;
     }
@@ -256,7 +253,6 @@ Grids grids_for(const pxcl_ctx* ctx, u32 wg, u32 mpw, u64 digis, u64 present, u3
     const u64 ch = seg_chunk(flags);
     g.a = u32(std::max<u64>(1, std::min<u64>(fa, (digis + ch - 1) / ch + k)));
     g.b = u32(std::max<u64>(1, std::min<u64>(fb, digis / (dcap + 1))));
-    g.x = u32(std::max<u64>(1, std::min<u64>(fx, digis / (BIG_RCAP + 1))));
     g.s = u32(std::max<u64>(1, std::min<u64>(fs, (present + mpw - 1) / mpw)));
     // compaction: a wave per 64 modules, or several when that fills less than the device
     const u64 blocks = u64(k) * ((ctx->n_modules + 63) / 64);
@@ -274,7 +270,7 @@ hipError_t launch_all(const LaunchArgs& a, const Grids& g, u32 wg, u32 mpw, hipS
     if (tev && (e = hipEventRecord(tev[1], s)) != hipSuccess) return e;
     if ((e = launch_small(wg, mpw, a, g.s, s)) != hipSuccess) return e;   // lists the big modules
     if (tev && (e = hipEventRecord(tev[2], s)) != hipSuccess) return e;
-    if (!(a.flags & LF_NO_BIG) && (e = launch_big(a, g.b, g.x, s)) != hipSuccess) return e;
+    if (!(a.flags & LF_NO_BIG) && (e = launch_big(a, g.b, s)) != hipSuccess) return e;
     if (tev && (e = hipEventRecord(tev[3], s)) != hipSuccess) return e;
     if ((e = launch_compact(a, g.c, s)) != hipSuccess) return e;
     if (tev && (e = hipEventRecord(tev[4], s)) != hipSuccess) return e;
@@ -428,7 +424,7 @@ thread_local int t_in_callback = 0;
 // kernels and the compaction, on the event's stream, then its completion event again.
 bool relaunch_deferred(pxcl_event* ev) {
     const LaunchArgs& a = ev->defer_args;
-    hipError_t e = launch_big(a, ev->defer_grid_b, ev->defer_grid_x, ev->stream);
+    hipError_t e = launch_big(a, ev->defer_grid_b, ev->stream);
     if (e == hipSuccess) e = launch_compact(a, ev->defer_grid_c, ev->stream);
     if (e == hipSuccess) e = hipEventRecord(ev->done_ev, ev->stream);
     if (e != hipSuccess) {
@@ -469,7 +465,7 @@ bool event_complete(void* p) {
 // The second launch of a batch whose big-module kernels were deferred.
 bool relaunch_deferred(pxcl_batch* b) {
     const LaunchArgs& a = b->defer_args;
-    hipError_t e = launch_big(a, b->defer_grid_b, b->defer_grid_x, b->stream);
+    hipError_t e = launch_big(a, b->defer_grid_b, b->stream);
     if (e == hipSuccess) e = launch_compact(a, b->defer_grid_c, b->stream);
     if (e == hipSuccess) e = hipEventRecord(b->done_ev, b->stream);
     if (e != hipSuccess) {
@@ -815,7 +811,6 @@ extern "C" int pxcl_acquire(pxcl_event* ev, const pxcl_digis* in, void* stream, 
         ev->defer_args = a;
         ev->defer_args.flags &= ~(LF_NO_BIG | LF_NO_SCRATCH | LF_DEFER);
         ev->defer_grid_b = g.b;
-        ev->defer_grid_x = g.x;
         ev->defer_grid_c = g.c;
     }
     if (e == hipSuccess) e = launch_all(a, g, wg, mpw, s, timed ? ev->tev : nullptr);
@@ -1449,7 +1444,6 @@ extern "C" int pxcl_acquire_batch(pxcl_batch* b, pxcl_event* const* evs, const p
             b->defer_args = batch_args(b, wg, mpw);
             b->defer_args.flags = (lflags & ~(LF_NO_BIG | LF_NO_SCRATCH | LF_DEFER)) | LF_SECOND;
             b->defer_grid_b = g.b;
-            b->defer_grid_x = g.x;
             b->defer_grid_c = g.c;
         }
         if (graph) {

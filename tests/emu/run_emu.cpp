@@ -115,7 +115,7 @@ int main(int argc, char** argv) {
     if (stale_ticket) a.ctr[S_TICK] = 1000003u;
     if (((a.flags & LF_GROUP) && launch_group(a, h[5], h[5], h[5], nullptr)) ||
         (!(a.flags & (LF_FUSED | LF_NO_SEG)) && launch_segment(a, h[5], nullptr)) || launch_small(h[3], h[4], a, h[7], nullptr) ||
-        (!(a.flags & LF_NO_BIG) && launch_big(a, h[6], h[6], nullptr)) || launch_compact(a, h[8], nullptr)) {
+        (!(a.flags & LF_NO_BIG) && launch_big(a, h[6], nullptr)) || launch_compact(a, h[8], nullptr)) {
         fprintf(stderr, "launch failed\n");
         return 3;
     }
@@ -135,7 +135,7 @@ int main(int argc, char** argv) {
     if (second) {
         LaunchArgs a2 = a;
         a2.flags = (a.flags & ~(LF_NO_BIG | LF_NO_SCRATCH | LF_DEFER)) | (a.hdr ? LF_SECOND : 0u);
-        if (launch_big(a2, h[6], h[6], nullptr) || launch_compact(a2, h[8], nullptr)) {
+        if (launch_big(a2, h[6], nullptr) || launch_compact(a2, h[8], nullptr)) {
             fprintf(stderr, "second launch failed\n");
             return 3;
         }
