@@ -475,7 +475,7 @@ int pxcl_serve(pxcl_ctx* ctx, void* d_arena, size_t arena_bytes, void* h_pinned,
  * wrong results.  Calls in one stream, or otherwise ordered, are safe; after a
  * failed launch the next call clears the control words with a kernel first. */
 #define PXCL_NOALLOC_MAX_DIGIS 262144u
-#define PXCL_NOALLOC_SCRATCH_BYTES 15972352u
+#define PXCL_NOALLOC_SCRATCH_BYTES 14923776u
 typedef struct {
     int32_t* digi_cluster;
     int32_t* id;

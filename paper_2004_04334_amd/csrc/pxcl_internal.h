@@ -210,11 +210,10 @@ struct EvLayout {
     size_t mtab;                             // per module: ModRange
     size_t kept;                             // per module: kept clusters
     size_t big;                              // module ids for the big-module kernel
-    size_t scr;                              // module ids for the scratch-mode kernel
+    size_t scr;                              // module ids for the big-module kernel's scratch mode
     size_t present;                          // module ids of the modules present (any order)
     size_t off;                              // per module: its first cluster in the outputs
     size_t hit_x, hit_y;                     // hits (per kept cluster), when asked for
-    size_t perm;                             // (4N bytes, not used)
     size_t grp;                              // digis in any order: the grouped copy (u64[N])
     size_t gcnt;                             // digis in any order: per module, digis counted (zero between launches)
     size_t hsum;                             // fused hits: per staged record, sum(adc*col), sum(adc*row) (u64)
@@ -251,10 +250,9 @@ PXCL_HD constexpr EvLayout ev_layout(u32 N, u32 M) {
     const size_t opt = mod + 5 * m4;
     L.hit_x = opt;
     L.hit_y = opt + n4;
-    L.perm = opt + 2 * n4;
-    L.grp = opt + 3 * n4;
-    L.gcnt = opt + 3 * n4 + n8;
-    L.hsum = opt + 3 * n4 + n8 + m4;
+    L.grp = opt + 2 * n4;
+    L.gcnt = opt + 2 * n4 + n8;
+    L.hsum = opt + 2 * n4 + n8 + m4;
     L.total = L.hsum + al256(16 * size_t(N));
     return L;
 }

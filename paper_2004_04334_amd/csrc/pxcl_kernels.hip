@@ -67,12 +67,6 @@ __device__ __forceinline__ u32 ld_ag(const u32* p) {
 __device__ __forceinline__ void st_ag(u32* p, u32 v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ u64 ld_ag64(const u64* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_ag64(u64* p, u64 v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ void st_sys(u32* p, u32 v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
@@ -210,11 +204,10 @@ __device__ __forceinline__ u32 find_slot(const u32* pref, u32 k, u32 t) {
     return wave_uniform(u32(__popcll(__ballot(in0 ? 1 : 0)) + __popcll(__ballot(in1 ? 1 : 0))) - 1u);
 }
 
-// What event_prefix counts per event: its digis (CNT_DIGIS), the digis of an event
-// grouped by module (CNT_SORTED: zero for digis in any order) or in any order
-// (CNT_ANY: zero for grouped ones), the modules per event, its work units.
-constexpr u32 CNT_DIGIS = 0, CNT_MODULES = 0xFFFFFFFFu, CNT_UNITS = 0xFFFFFFFEu, CNT_SORTED = 0xFFFFFFFDu,
-              CNT_ANY = 0xFFFFFFFCu;
+// What event_prefix counts per event: its work units, the digis of an event grouped by
+// module (CNT_SORTED: zero for digis in any order) or in any order (CNT_ANY: zero for grouped
+// ones).
+constexpr u32 CNT_UNITS = 0xFFFFFFFEu, CNT_SORTED = 0xFFFFFFFDu, CNT_ANY = 0xFFFFFFFCu;
 
 // Modules on the event's present-module list.
 __device__ __forceinline__ u32 present_count(const LaunchArgs& a, const EventDesc& E) {
@@ -237,9 +230,8 @@ __device__ __forceinline__ u32 unit_module(const LaunchArgs& a, const EventDesc&
 }
 
 // Prefix over the events of a launch of max(ceil(count / div), at_least) + plus,
-// where count is the event's digis (CNT_DIGIS), the modules per event
-// (CNT_MODULES), its work units (CNT_UNITS) or one of its control words (CTL_*, at
-// most the modules per event); 0 for an empty event.  pref[k] = total.
+// where count is one of the above or one of its control words (CTL_*, at most the modules
+// per event); 0 for an empty event.  pref[k] = total.
 // Every thread of the workgroup calls it; any k <= MAXB with any BS.
 template <u32 BS>
 __device__ __forceinline__ u32 event_prefix(const LaunchArgs& a, u32 k, u32* pref, u32* wsum, u32 which, u32 div,
@@ -252,12 +244,10 @@ __device__ __forceinline__ u32 event_prefix(const LaunchArgs& a, u32 k, u32* pre
             const EventDesc E = get_event(a, e);
             u32 cnt = 0;
             if (E.n)
-                cnt = which == CNT_DIGIS     ? E.n
-                      : which == CNT_SORTED  ? ((E.flags & EF_UNSORTED) ? 0u : E.n)
-                      : which == CNT_ANY     ? ((E.flags & EF_UNSORTED) ? E.n : 0u)
-                      : which == CNT_MODULES ? a.n_modules
-                      : which == CNT_UNITS   ? unit_count(a, E)
-                                             : min(ld_ag(ws_ptr<u32>(E, ev_layout(E.cap, a.n_modules).ctl) + which), a.n_modules);
+                cnt = which == CNT_SORTED  ? ((E.flags & EF_UNSORTED) ? 0u : E.n)
+                      : which == CNT_ANY   ? ((E.flags & EF_UNSORTED) ? E.n : 0u)
+                      : which == CNT_UNITS ? unit_count(a, E)
+                                           : min(ld_ag(ws_ptr<u32>(E, ev_layout(E.cap, a.n_modules).ctl) + which), a.n_modules);
             v = max((cnt + div - 1) / div, at_least) + plus;
         }
         u32 tot;

@@ -74,8 +74,7 @@ int main(int argc, char** argv) {
         if (any) {                        // the kernels read the raw digis and cluster a grouped copy
             d.flags |= EF_UNSORTED;
             d.r_module = d.module; d.r_row = d.row; d.r_col = d.col; d.r_adc = d.adc;
-            const u16* g = reinterpret_cast<const u16*>(ws[e] + L.grp);
-            d.module = g; d.row = g + cap; d.col = g + 2 * size_t(cap); d.adc = g + 3 * size_t(cap);
+            d.module = d.row = d.col = d.adc = nullptr;
         }
         d.ws = ws[e];
         d.hstat = hs[e];
