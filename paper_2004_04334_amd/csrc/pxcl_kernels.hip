@@ -1475,7 +1475,8 @@ struct DenseSmem {
 
 // This thread's index, worked out anew for every module (the second term is zero): addresses
 // that depend on the index alone would be computed before the loop over the modules, for
-// both modes, and spilled (21 registers, reloaded from memory between LDS phases).
+// both modes, and spilled (21 registers, reloaded from memory between LDS phases; 12 still are,
+// with the 128 a lane that sixteen waves of one compute unit can have).
 template <u32 WG>
 __device__ __forceinline__ u32 thread_in_loop(const Item& I) {
     return (threadIdx.x + (I.n >> 31)) & (WG - 1u);
@@ -1639,9 +1640,9 @@ __device__ __forceinline__ void cluster_dense(const LaunchArgs& a, const EventDe
 // event's final charge/size arrays, which the compaction kernel overwrites later, for the
 // rest), leaving each digi's cluster in its output word; per-digi ids from that.  The passes
 // take four digis per load and test the ranges of four at once.  Like register mode it is
-// bound by the instructions of one workgroup: a serpentine 159 -> 75 us (before: unions
-// column by column, a lane per row, 60-85 us of it; one digi per load; runs looked up again
-// for the ids).
+// bound by the instructions of one workgroup: a serpentine alone in the launch 159 -> 71 us
+// along rows, 49 us along columns (before: unions column by column, a lane per row, 60-85 us of
+// it; one digi per load; runs looked up again for the ids).
 template <u32 BW>
 struct BigScratchSmem {
     u32 bm[BM_WORDS];
@@ -2108,9 +2109,10 @@ __device__ __forceinline__ Item big_item(const LaunchArgs& a, const u32* s_pref,
 // take longest, then those of the big-module list.  A workgroup's first module is given by its
 // index, the others by ticket, so a workgroup busy with a scratch-mode module takes no more
 // than that while the rest share the others.  16 events with a serpentine and 16-20 modules
-// of 2,049 to 13,312 digis each: 92 us, where a launch per mode took 57 + 82 (118 us with
-// tickets drawn when a module starts: those of the scratch-mode workgroups waited with them);
-// launched for no module at all it costs one launch instead of two.
+// of 2,049 to 13,312 digis each: 92 us, where a launch per mode took 57 + 82 with the same code
+// for the modules (118 us with tickets drawn when a module starts: those of the scratch-mode
+// workgroups waited with them), 81 us since; launched for no module at all it costs one launch
+// instead of two.
 static_assert(B_WG == S_WG, "the modes share the workgroup");
 __global__ __launch_bounds__(B_WG) void k_big(LaunchArgs a) {
     __shared__ union {
@@ -2383,8 +2385,8 @@ __global__ __launch_bounds__(F_WG) void k_fill(u32* p, u32 n, u32 v) {
 // it, an engine's start and its completion signal), so one launch moves them all, every
 // thread with C_UNR words of any of them in flight.  The host's end is accessed at system
 // scope: neither side may see the other's data through a cache it cannot see written.
-// Four input and six output arrays of a 50,000-digi event: 185 -> 101 us for the whole
-// chain of which they are part.
+// Four input and six output arrays of a 50,000-digi event, in new buffers or used ones: the
+// whole chain of which they are part takes 101 us instead of 173 with a copy command each.
 // ---------------------------------------------------------------------------
 constexpr u32 CP_WG = 256, C_UNR = 4;
 template <bool TO_HOST>

@@ -82,10 +82,11 @@ int status_from_bits(u32 bits) {
     return PXCL_OK;
 }
 
-// Host copies of at most this many bytes go by one kernel (a chain of pinned digis in,
-// clusters and hits out: 50,000 digis 242 -> 163 us, 2,000 digis 144 -> 127 us, 400,000 digis,
-// 12 MB, 450 -> 384 us); above, nothing is left to gain and the copy engines need no compute
-// units.
+// Host copies of at most this many bytes go by one kernel.  A chain of pinned digis in, clusters
+// and hits out (1,856 modules of random pixels, shape 64x1), by copy commands -> by kernel: 2,000
+// digis 91 -> 87 us, 50,000 173 -> 101, 400,000 329 -> 251, 1 million 677 -> 621, 2 million
+// (15 MB in, 27 out) 1,120 -> 1,078 with both by kernel; 4 million 2,039 -> 2,016: little is left
+// to gain above, and the copy engines need no compute units.
 constexpr size_t KERNEL_COPY_BYTES = size_t(16) << 20;
 
 // A launch whose completion event the completion thread polls.
