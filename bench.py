@@ -604,8 +604,9 @@ def bench_serve(px, torch, args, evs):
     batches = [px.Batch(ctx, max_batch) for _ in range(n_b)]
     streams = [torch.cuda.Stream() for _ in range(n_b)]
     tuned = tune(px, ctx, args, evs[:16], pool[:16])      # a typical continuous batch
-    # results are consumed at the callback only, so batches defer the big-module
-    # kernels to a second launch that a batch gets only when one of its events needs it;
+    # results are consumed at the callback only, so batches may defer the big-module
+    # kernel to a second launch that a batch gets only when one of its events needs it
+    # (while nearly all do, as at the 256-thread shape, the driver launches them whole);
     # plain launches: a graph replay now and then holds the launching thread (the
     # dispatcher) for milliseconds, a few small kernel launches do not
     common = dict(budget_bytes=16 << 30, n_slots=n_slots, max_batch=max_batch, n_cpu_threads=16,
@@ -649,7 +650,7 @@ def bench_serve(px, torch, args, evs):
         "saturated_events_per_s": round(sat, 1), "runs": runs,
         "config": {"workload": "serve: Poisson arrivals, 10k-200k digis/event, 16 GB admission budget, "
                                "continuous batching over 8 streams with at most 6 batches on the device "
-                               "(plain launches, big-module kernels deferred to a second launch when needed), "
+                               "(plain launches, big-module kernel deferred while few batches need it), "
                                "16 CPU threads with 20 us synthetic tasks",
                    "requests_per_run": SERVE_REQUESTS, "kernel_config": shape,
                    "autotune_us": tuned, "value_is": "the run at 0.7 of the saturated rate",

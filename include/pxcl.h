@@ -337,7 +337,7 @@ int pxcl_batch_query(const pxcl_batch* b);
 
 /* ---- autotuning ---------------------------------------------------------------- */
 /* Time every kernel configuration (wg x mpw) on the given batch (reps replays each,
- * blocking: a setup-time call), select the fastest, and, if cache_path is not NULL,
+ * blocking and whole, nothing deferred: a setup-time call), select the fastest, and, if cache_path is not NULL,
  * record it in that JSON file under a key of device architecture and shape bucket.
  * us_out (may be NULL) receives 12 mean times in microseconds, wg-major
  * (64,128,256,512) x mpw (1,2,4); invalid combinations report -1. */
