@@ -337,8 +337,9 @@ int pxcl_batch_query(const pxcl_batch* b);
 
 /* ---- autotuning ---------------------------------------------------------------- */
 /* Time every kernel configuration (wg x mpw) on the given batch (reps replays each,
- * blocking and whole, nothing deferred: a setup-time call), select the fastest, and, if cache_path is not NULL,
- * record it in that JSON file under a key of device architecture and shape bucket.
+ * blocking and whole, nothing deferred: a setup-time call), select the fastest, and, if
+ * cache_path is not NULL, record it in that JSON file under a key of device architecture and
+ * shape bucket.
  * us_out (may be NULL) receives 12 mean times in microseconds, wg-major
  * (64,128,256,512) x mpw (1,2,4); invalid combinations report -1. */
 int pxcl_autotune(pxcl_ctx* ctx, pxcl_batch* b, pxcl_event* const* evs, const pxcl_digis* ins,
